@@ -11,6 +11,13 @@ namespace gr {
 template <int DT> struct Chunk;
 template <> struct Chunk<GR_F32> {
     static constexpr int E = 4;
+    __device__ static inline uint4 raw(const void* X, int64_t row, int K, int q) {
+        return *reinterpret_cast<const uint4*>((const float*)X + row * K + q * 4);
+    }
+    __device__ static inline void unpack(const uint4& t, float* v) {
+        v[0] = __uint_as_float(t.x); v[1] = __uint_as_float(t.y);
+        v[2] = __uint_as_float(t.z); v[3] = __uint_as_float(t.w);
+    }
     __device__ static inline void load(const void* X, int64_t row, int K, int q, float* v) {
         float4 t = *reinterpret_cast<const float4*>((const float*)X + row * K + q * 4);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
@@ -22,8 +29,13 @@ template <> struct Chunk<GR_F32> {
 };
 template <> struct Chunk<GR_BF16> {
     static constexpr int E = 8;
+    __device__ static inline uint4 raw(const void* X, int64_t row, int K, int q) {
+        return *reinterpret_cast<const uint4*>((const uint16_t*)X + row * K + q * 8);
+    }
     __device__ static inline void load(const void* X, int64_t row, int K, int q, float* v) {
-        uint4 t = *reinterpret_cast<const uint4*>((const uint16_t*)X + row * K + q * 8);
+        unpack(raw(X, row, K, q), v);
+    }
+    __device__ static inline void unpack(const uint4& t, float* v) {
         uint32_t u[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {

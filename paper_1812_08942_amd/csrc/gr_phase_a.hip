@@ -1180,6 +1180,15 @@ int init_vectors(int64_t n, int32_t K, uint64_t seed, int32_t dtype, const int32
 // partial sums are combined by a fixed shuffle tree inside the wave and,
 // for rows wider than a wave, across its waves in LDS.
 constexpr int kU = 4;
+// Slots past a row's end.  Rows of up to 8 kShortLanes entries (a round
+// covers half of them at least): such a slot repeats the row's last entry,
+// whose vector row another slot gathers anyway, and is skipped where no row
+// of the wave has it.  Reading the row's own vector there instead, with
+// weight 0, fetched it once more from memory for every row (256^3 grid, 64-
+// byte rows: smoothing 13.2 -> 12.4 ms per reduction).  On wider rows, whose
+// slots are mostly in range, the branches cost more than the few own rows
+// (power law 11.77 -> 11.87 ms), so those keep the plain loop.
+constexpr int kShortLanes = 4;
 // threads of a smoothing block (measured: 512 beats 1024 by 0.5 ms per
 // reduction on the power-law graph; 256 loses 1.1 ms)
 #ifndef GR_GS_BLOCK
@@ -1241,24 +1250,54 @@ __device__ inline void gs_block(const int32_t* __restrict__ rp, const int32_t* _
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = 0.0f;
     float d = 0.0f;
-    for (int32_t e = e0 + p; e < e1; e += kU * P) {
-        int32_t j[kU];
-        float wt[kU];
+    if (L <= kShortLanes * Q) {  // block-uniform
+        for (int32_t e = e0 + p; e < e1; e += kU * P) {
+            int32_t j[kU];
+            float wt[kU];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            int32_t eu = e + u * P;
-            bool ok = eu < e1;
-            j[u] = ok ? col[eu] : (int32_t)r;   // out of range: weight 0, own row
-            wt[u] = ok ? w[eu] : 0.0f;
+            for (int u = 0; u < kU; ++u) {
+                const int32_t eu = min(e + u * P, e1 - 1);
+                j[u] = col[eu];
+                wt[u] = w[eu];
+            }
+            // all columns have arrived before the first branch, so that no
+            // branch waits for the gathers before it
+#pragma unroll
+            for (int u = 0; u < kU; ++u) asm volatile("" : "+v"(j[u]));
+            uint4 raw[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (u == 0 || __any(e + u * P < e1)) raw[u] = Chunk<DT>::raw(X, j[u], K, q);
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (e + u * P < e1) {
+                    float x[E];
+                    Chunk<DT>::unpack(raw[u], x);
+#pragma unroll
+                    for (int i = 0; i < E; ++i) acc[i] = __fmaf_rn(wt[u], x[i], acc[i]);
+                    d += wt[u];
+                }
         }
-        float x[kU][E];
+    } else {
+        for (int32_t e = e0 + p; e < e1; e += kU * P) {
+            int32_t j[kU];
+            float wt[kU];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) Chunk<DT>::load(X, j[u], K, q, x[u]);
+            for (int u = 0; u < kU; ++u) {
+                int32_t eu = e + u * P;
+                bool ok = eu < e1;
+                j[u] = ok ? col[eu] : (int32_t)r;   // out of range: weight 0, own row
+                wt[u] = ok ? w[eu] : 0.0f;
+            }
+            float x[kU][E];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
+            for (int u = 0; u < kU; ++u) Chunk<DT>::load(X, j[u], K, q, x[u]);
 #pragma unroll
-            for (int i = 0; i < E; ++i) acc[i] = __fmaf_rn(wt[u], x[u][i], acc[i]);
-            d += wt[u];
+            for (int u = 0; u < kU; ++u) {
+#pragma unroll
+                for (int i = 0; i < E; ++i) acc[i] = __fmaf_rn(wt[u], x[u][i], acc[i]);
+                d += wt[u];
+            }
         }
     }
     // combine the slots of the row inside the wave
