@@ -13,6 +13,7 @@
 #include "gr_internal.hpp"
 
 #include <math.h>
+#include <string.h>
 
 #include <vector>
 
@@ -24,7 +25,9 @@ constexpr int kRedBlocks = 256;
 // scalar slots on the device
 enum {
     SC_RZ = 0, SC_PQ, SC_RR, SC_BB, SC_TMP, SC_LAMN, SC_LAMN0, SC_ETA, SC_ETAMAX, SC_LAM1,
-    SC_MAXS, SC_SUMW0, SC_HLH, SC_COUNT
+    SC_MAXS, SC_SUMW0, SC_HLH, SC_COUNT,
+    SC_STATUS = 24,  // two words: the status of the resident solves
+    SC_WORDS = 26
 };
 
 __device__ inline double block_reduce_sum(double v, double* sh) {
@@ -200,6 +203,425 @@ __global__ void k_copy_scalar(double* __restrict__ sc, int from, int to) {
     if (threadIdx.x == 0 && blockIdx.x == 0) sc[to] = sc[from];
 }
 
+// ------------------------------------------------- CG in one launch
+// The whole solve on graphs of up to kResN nodes.  Launch by launch, an
+// iteration is eight dependent launches and its time is theirs (31 us at
+// 13,000 nodes and 280,000 entries, whatever the kernels do); here
+// kResBlocks workgroups stay resident (cooperative launch) and meet twice
+// per iteration, which then takes 8 us (product 1.3, meetings 1.9 and 2.9,
+// the last with the gather of z, 1.5 to form p), bound by the latency of the
+// device-coherent exchanges.  Larger graphs, and those whose hub rows do not
+// fit a workgroup, are solved launch by launch.
+//  * Workgroup b owns the rows b, b + kResBlocks, .. (graphs are often
+//    numbered by degree: consecutive rows put every hub into one workgroup):
+//    y, r, z, p and d of a row stay in its thread's registers, and every
+//    workgroup keeps all of p in LDS, workgroup by workgroup.
+//  * The rows' entries are cut into pieces of kResG * kResU = 32, a group of
+//    16 lanes each; the first kResSlots pieces of a lane group stay in
+//    registers for the whole solve, further ones are read again each time.
+//    A row's owner adds its piece sums in order.
+//  * The product needs p of all rows.  Only z is passed on: once beta is
+//    known everyone forms p = z + beta p in its LDS copy, by the same
+//    operation as the owner, so p needs no meeting of its own.
+//  * A meeting is a reduction: every workgroup publishes its partial sums in
+//    slots of its own, and a wave of every workgroup reads all slots until
+//    none is empty, and adds them in one fixed tree.  Slots and z move by
+//    device-coherent relaxed atomics; no fence writes back or drops a cache.
+//    A value is its own flag: kResEmpty (a NaN that no sum is allowed to
+//    have) means not there yet.  Waiting for z to be stored before the sums
+//    are published cost 2 us of each iteration.
+//  * Emptying.  Slots go round in four epochs: a workgroup empties its slot
+//    of epoch e + 2 once epoch e is complete (all have then passed e - 1 and
+//    with it e - 2).  z has two buffers: once the product's meeting of
+//    iteration i + 1 is complete everyone has read z of iteration i, and it
+//    is emptied.  Every publication of a product's sum first waits for the
+//    thread's stores, and comes between an emptying and the next use.
+//  * Every wait is bounded; past it the call fails.
+// A meeting of 64 workgroups takes 1.5 us when each has a line of its own for
+// its slots, 2.1 us when the slots share lines; counting arrivals and reading
+// the sums afterwards takes 2.2 us.
+constexpr int kResBlocks = 64;
+constexpr int kResThreads = 1024;
+constexpr int kResN = 16384;
+constexpr int64_t kResNnz = 4 << 20;
+constexpr int kResG = 16, kResU = 2, kResPiece = kResG * kResU;
+constexpr int kResGroups = kResThreads / kResG;
+constexpr int kResSlots = 4;
+constexpr int kResRows = kResN / kResBlocks;  // rows of a workgroup at most
+constexpr int kResPieces = 2048;              // pieces of a workgroup at most
+constexpr unsigned kResSpin = 1u << 21;
+constexpr int kResEpochs = 4;
+constexpr int kResLine = 8;  // words from one workgroup's slots to the next's: a line each
+constexpr size_t kResSlotWords = (size_t)kResEpochs * kResBlocks * kResLine;
+constexpr unsigned long long kResEmpty = ~0ull;
+// status words: what went wrong, and the longest solve
+enum { RES_FLAGS = 0, RES_ITERS, RES_ABORT, RES_WORDS = 4 };
+static_assert(SC_STATUS >= SC_COUNT && (SC_WORDS - SC_STATUS) * 8 == RES_WORDS * 4 && SC_WORDS <= 32,
+              "the status words lie behind the scalars");
+enum { RES_DIVERGED = 1, RES_TIMEOUT = 2, RES_UNFIT = 4 };
+
+// words of the slots and the two z buffers
+static size_t res_words(int64_t n) { return kResSlotWords + 2 * ((size_t)n + kResBlocks); }
+
+__device__ inline unsigned long long ld_agent(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void st_agent(unsigned long long* p, unsigned long long v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline unsigned long long res_bits(double v) {
+    return v == v ? (unsigned long long)__double_as_longlong(v) : 0x7ff8000000000000ull;
+}
+__device__ inline double res_value(unsigned long long u) { return __longlong_as_double((long long)u); }
+
+// sum over aligned groups of 16 lanes, in every lane
+template <int CTRL>
+__device__ inline double dpp_add(double v) {
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(x >> 32), (int)(x >> 32), CTRL, 0xf, 0xf, false);
+    return v + __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+__device__ inline double sum16(double v) {
+    v = dpp_add<0xB1>(v);   // lane ^ 1
+    v = dpp_add<0x4E>(v);   // lane ^ 2
+    v = dpp_add<0x141>(v);  // mirrored halves of 8
+    return dpp_add<0x140>(v);  // mirrored 16
+}
+__device__ inline double lane_value(double v, int lane) {
+    const long long x = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)x, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(x >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ inline double sum_wave(double v) {
+    v = sum16(v);
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+struct ResShared {
+    alignas(16) double p[kResN];
+    double piece[kResPieces];
+    double red[2][kResThreads / kWave];
+    double sum[2];
+    int32_t ppos[kResRows + 1];
+    uint16_t prow[kResPieces];
+    int32_t stop;
+};
+
+struct ResMeet {
+    unsigned long long* slots;
+    int32_t* status;
+    unsigned epoch;
+
+    // publishes the workgroup's sums of a and b (one pair per thread)
+    __device__ inline void publish(ResShared& sh, double a, double b) {
+        const int tid = threadIdx.x, lane = tid & (kWave - 1);
+        a = sum_wave(a);
+        b = sum_wave(b);
+        if (lane == 0) {
+            sh.red[0][tid / kWave] = a;
+            sh.red[1][tid / kWave] = b;
+        }
+        __syncthreads();
+        static_assert(kResThreads / kWave == 16, "sums of 16 lanes");
+        if (tid < 32) {
+            const double t = sum16(sh.red[tid / 16][tid % 16]);
+            if (tid % 16 == 0)
+                st_agent(at(epoch, blockIdx.x) + tid / 16, res_bits(t));
+        }
+    }
+    // the sums over all workgroups, by the first wave, into shared memory
+    __device__ inline void collect(ResShared& sh) {
+        const int lane = threadIdx.x & (kWave - 1);
+        const unsigned long long* mine = at(epoch, lane);
+        unsigned long long u = kResEmpty, v = kResEmpty;
+        bool ok = false;
+        for (unsigned it = 0; it < kResSpin; ++it) {
+            if (u == kResEmpty) u = ld_agent(mine);
+            if (v == kResEmpty) v = ld_agent(mine + 1);
+            ok = __ballot(u == kResEmpty || v == kResEmpty) == 0;
+            if (ok || ((it & 1023u) == 1023u && aborted())) break;
+        }
+        const double x = sum_wave(res_value(u)), y = sum_wave(res_value(v));
+        if (lane == 0) {
+            sh.sum[0] = x;
+            sh.sum[1] = y;
+            if (!ok) abandon(sh);
+        }
+        if (lane < 2) st_agent(at(epoch + 2, blockIdx.x) + lane, kResEmpty);
+    }
+    // all threads: waits for the sums; false when a wait ran out, here or
+    // elsewhere
+    __device__ inline bool result(ResShared& sh, double* sa, double* sb) {
+        __syncthreads();
+        ++epoch;
+        *sa = sh.sum[0];
+        *sb = sh.sum[1];
+        return !sh.stop;
+    }
+    __device__ inline bool meet(ResShared& sh, double a, double b, double* sa, double* sb) {
+        publish(sh, a, b);
+        if (threadIdx.x < kWave) collect(sh);
+        return result(sh, sa, sb);
+    }
+    __device__ inline unsigned long long* at(unsigned e, int blk) {
+        return slots + ((size_t)(e % kResEpochs) * kResBlocks + blk) * kResLine;
+    }
+    __device__ inline bool aborted() {
+        return __hip_atomic_load(status + RES_ABORT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    }
+    __device__ inline void abandon(ResShared& sh) {
+        sh.stop = 1;
+        atomicOr(status + RES_FLAGS, (int)RES_TIMEOUT);
+        __hip_atomic_store(status + RES_ABORT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+static_assert(kResBlocks == kWave, "a lane per slot");
+
+// The z of all rows, two neighbouring values per load, one load of a thread
+// kResThreads pairs from the next: all of a thread's loads are in flight
+// together (as 8-byte loads in two rounds the gather took 3 us at 13,000
+// rows).  Each half of a load is a whole value or empty.
+typedef unsigned res_v4 __attribute__((ext_vector_type(4)));
+constexpr int kResF = kResN / 2 / kResThreads;
+static_assert(kResF == 8, "the loads below");
+__device__ inline void res_load(const unsigned long long* z, int32_t m, res_v4* t) {
+    unsigned o[kResF];
+#pragma unroll
+    for (int u = 0; u < kResF; ++u)
+        o[u] = 16u * (unsigned)min((int)threadIdx.x + u * kResThreads, m / 2 - 1);
+    // waits for its own loads: none is in flight past the block
+    if (m <= kResN / 2) {
+        asm volatile(
+            "global_load_dwordx4 %0, %4, %8 sc1\n\tglobal_load_dwordx4 %1, %5, %8 sc1\n\t"
+            "global_load_dwordx4 %2, %6, %8 sc1\n\tglobal_load_dwordx4 %3, %7, %8 sc1\n\t"
+            "s_waitcnt vmcnt(0)"
+            : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3])
+            : "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "s"(z)
+            : "memory");
+        t[4] = t[5] = t[6] = t[7] = t[0];
+    } else {
+        asm volatile(
+            "global_load_dwordx4 %0, %8, %16 sc1\n\tglobal_load_dwordx4 %1, %9, %16 sc1\n\t"
+            "global_load_dwordx4 %2, %10, %16 sc1\n\tglobal_load_dwordx4 %3, %11, %16 sc1\n\t"
+            "global_load_dwordx4 %4, %12, %16 sc1\n\tglobal_load_dwordx4 %5, %13, %16 sc1\n\t"
+            "global_load_dwordx4 %6, %14, %16 sc1\n\tglobal_load_dwordx4 %7, %15, %16 sc1\n\t"
+            "s_waitcnt vmcnt(0)"
+            : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]),
+              "=&v"(t[6]), "=&v"(t[7])
+            : "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "v"(o[4]), "v"(o[5]), "v"(o[6]),
+              "v"(o[7]), "s"(z)
+            : "memory");
+    }
+}
+// one value, waited for when it was not there yet
+__device__ inline unsigned long long res_wait(ResShared& sh, ResMeet& meet,
+                                              const unsigned long long* at, unsigned lo,
+                                              unsigned hi) {
+    unsigned long long v = ((unsigned long long)hi << 32) | lo;
+    for (unsigned it = 0; v == kResEmpty; ++it) {
+        if (it >= kResSpin || ((it & 1023u) == 1023u && meet.aborted())) {
+            meet.abandon(sh);
+            break;
+        }
+        v = ld_agent(at);
+    }
+    return v;
+}
+// p = z + beta p (first: p = z)
+__device__ inline void res_take(ResShared& sh, ResMeet& meet, const unsigned long long* z,
+                                int32_t m, res_v4* t, double beta, bool first) {
+    bool late = false;
+#pragma unroll
+    for (int u = 0; u < kResF; ++u)
+        late = late || (t[u].x & t[u].y) == ~0u || (t[u].z & t[u].w) == ~0u;
+    if (__any(late)) {
+#pragma unroll
+        for (int u = 0; u < kResF; ++u) {
+            const int j = min(2 * ((int)threadIdx.x + u * kResThreads), m - 2);
+            const unsigned long long a = res_wait(sh, meet, z + j, t[u].x, t[u].y);
+            const unsigned long long b = res_wait(sh, meet, z + j + 1, t[u].z, t[u].w);
+            t[u] = res_v4{(unsigned)a, (unsigned)(a >> 32), (unsigned)b, (unsigned)(b >> 32)};
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kResF; ++u) {
+        const int j = 2 * ((int)threadIdx.x + u * kResThreads);
+        if (j < m) {
+            const double a = res_value(((unsigned long long)t[u].y << 32) | t[u].x);
+            const double b = res_value(((unsigned long long)t[u].w << 32) | t[u].z);
+            double2* at = reinterpret_cast<double2*>(sh.p + j);
+            double2 v = *at;
+            v.x = first ? a : fma(beta, v.x, a);
+            v.y = first ? b : fma(beta, v.y, b);
+            *at = v;
+        }
+    }
+}
+
+// out = L_P^+ b, b and out centred
+__global__ void __launch_bounds__(kResThreads) k_cg_resident(
+    const int32_t* __restrict__ rp, const int32_t* __restrict__ col, const double* __restrict__ w,
+    const double* __restrict__ diag, int32_t n, const double* __restrict__ b, double* __restrict__ out,
+    unsigned long long* words, int32_t* status, int32_t cg_max, double tol2) {
+    __shared__ ResShared sh;
+    ResMeet meet{words, status, 0u};
+    unsigned long long* const zbuf = words + kResSlotWords;
+    const int tid = threadIdx.x, blk = blockIdx.x;
+    const int R = (n + kResBlocks - 1) / kResBlocks;  // at most kResRows
+    const int32_t m = R * kResBlocks;                 // positions; row v at (v % kResBlocks) R + v / kResBlocks
+    auto row_of = [blk](int t) { return t * kResBlocks + blk; };
+    auto place = [R](int32_t v) { return (v % kResBlocks) * R + v / kResBlocks; };
+    const bool own = tid < R && row_of(tid) < n;
+    const int grp = tid / kResG, gl = tid % kResG;
+    if (tid == 0) sh.stop = 0;
+    // offsets of the rows' pieces
+    static_assert(kResRows <= kResThreads && kResRows % kWave == 0, "a row per thread");
+    if (tid < kResRows) {
+        const int lane = tid & (kWave - 1);
+        int32_t t = own ? (rp[row_of(tid) + 1] - rp[row_of(tid)] + kResPiece - 1) / kResPiece : 0;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int32_t below = __shfl_up(t, off, kWave);
+            if (lane >= off) t += below;
+        }
+        sh.ppos[tid + 1] = t;  // inside the wave, so far
+    }
+    __syncthreads();
+    int32_t before = 0;  // pieces of the waves before this one
+    for (int v = kWave; v <= tid && v < kResRows; v += kWave) before += sh.ppos[v];
+    __syncthreads();
+    if (tid < kResRows) sh.ppos[tid + 1] += before;
+    if (tid == 0) sh.ppos[0] = 0;
+    __syncthreads();
+    const int np = sh.ppos[kResRows];
+    const bool fits = np <= kResPieces;
+    if (fits && own)
+        for (int k = sh.ppos[tid]; k < sh.ppos[tid + 1]; ++k) sh.prow[k] = (uint16_t)tid;
+    const double d = own ? diag[row_of(tid)] : 0.0;
+    double bi = own ? b[row_of(tid)] : 0.0, rz, bb, pq, rr, nz;
+    if (!meet.meet(sh, bi, 0.0, &rz, &nz)) return;
+    if (own) bi -= rz / (double)n;
+    double y = 0.0, r = bi, z = d > 0.0 ? bi / d : 0.0, p = z;
+    if (tid < R) st_agent(zbuf + m + blk * R + tid, res_bits(z));
+    // a workgroup whose pieces do not fit makes every one leave here
+    if (!meet.meet(sh, r * z, fits ? bi * bi : __builtin_nan(""), &rz, &bb)) return;
+    if (!(bb > 0.0)) {
+        if (own) out[row_of(tid)] = 0.0;
+        if (bb != bb && tid == 0 && blk == 0) atomicOr(status + RES_FLAGS, (int)RES_UNFIT);
+        return;
+    }
+    {
+        res_v4 t[kResF];
+        res_load(zbuf + m, m, t);
+        res_take(sh, meet, zbuf + m, m, t, 0.0, true);
+    }
+    // the register pieces, their columns as places in the copy of p
+    int32_t c[kResSlots][kResU];
+    double we[kResSlots][kResU];
+#pragma unroll
+    for (int k = 0; k < kResSlots; ++k) {
+        const int pc = grp + k * kResGroups;
+        int32_t e0 = 0, e1 = 0;
+        if (pc < np) {
+            const int t = sh.prow[pc];
+            e0 = rp[row_of(t)] + (pc - sh.ppos[t]) * kResPiece;
+            e1 = min(e0 + kResPiece, rp[row_of(t) + 1]);
+        }
+#pragma unroll
+        for (int u = 0; u < kResU; ++u) {
+            const int32_t e = e0 + gl + u * kResG;
+            c[k][u] = e < e1 ? place(col[e]) : 0;
+            we[k][u] = e < e1 ? w[e] : 0.0;
+        }
+    }
+    __syncthreads();
+    if (sh.stop) return;
+    int it = 0;
+    for (; it < cg_max; ++it) {
+        unsigned long long* const zold = zbuf + (size_t)((it + 1) & 1) * m;
+        unsigned long long* const znew = zbuf + (size_t)(it & 1) * m;
+#pragma unroll
+        for (int k = 0; k < kResSlots; ++k) {
+            const int pc = grp + k * kResGroups;
+            if (k * kResGroups < np) {  // workgroup-uniform
+                double s = 0.0;
+#pragma unroll
+                for (int u = 0; u < kResU; ++u) s = fma(we[k][u], sh.p[c[k][u]], s);
+                s = sum16(s);
+                if (gl == 0 && pc < np) sh.piece[pc] = s;
+            }
+        }
+        for (int k0 = kResSlots * kResGroups; k0 < np; k0 += kResGroups) {
+            const int pc = k0 + grp;
+            double s = 0.0;
+            if (pc < np) {
+                const int t = sh.prow[pc];
+                const int32_t e0 = rp[row_of(t)] + (pc - sh.ppos[t]) * kResPiece;
+                const int32_t e1 = min(e0 + kResPiece, rp[row_of(t) + 1]);
+#pragma unroll
+                for (int u = 0; u < kResU; ++u) {
+                    const int32_t e = e0 + gl + u * kResG;
+                    if (e < e1) s = fma(w[e], sh.p[place(col[e])], s);
+                }
+            }
+            s = sum16(s);
+            if (gl == 0 && pc < np) sh.piece[pc] = s;
+        }
+        __syncthreads();
+        double q = 0.0;
+        if (own) {
+            double s = 0.0;
+            int k = sh.ppos[tid];
+            const int k1 = sh.ppos[tid + 1];
+            for (; k + 4 <= k1; k += 4) {  // hub rows: four reads in flight
+                double t[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) t[u] = sh.piece[k + u];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) s += t[u];
+            }
+            for (; k < k1; ++k) s += sh.piece[k];
+            q = d * p - s;
+        }
+        // the emptied z and slots of the last iteration are stored
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (!meet.meet(sh, p * q, 0.0, &pq, &nz)) return;
+        const double alpha = pq != 0.0 ? rz / pq : 0.0;
+        y = fma(alpha, p, y);
+        r = fma(-alpha, q, r);
+        z = d > 0.0 ? r / d : 0.0;
+        if (tid < R) {
+            st_agent(znew + blk * R + tid, res_bits(z));
+            st_agent(zold + blk * R + tid, kResEmpty);
+        }
+        meet.publish(sh, r * z, r * r);
+        if (tid < kWave) meet.collect(sh);
+        res_v4 t[kResF];
+        res_load(znew, m, t);
+        if (!meet.result(sh, &nz, &rr)) return;
+        if ((it & 7) == 7) {
+            if (!(rr == rr)) {
+                if (tid == 0 && blk == 0) atomicOr(status + RES_FLAGS, (int)RES_DIVERGED);
+                return;
+            }
+            if (rr <= tol2 * bb) break;
+        }
+        const double beta = rz != 0.0 ? nz / rz : 0.0;
+        rz = nz;
+        p = fma(beta, p, z);
+        res_take(sh, meet, znew, m, t, beta, false);
+        __syncthreads();
+        if (sh.stop) return;
+    }
+    if (tid == 0 && blk == 0) atomicMax(status + RES_ITERS, it);
+    double sy;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (!meet.meet(sh, y, 0.0, &sy, &nz)) return;
+    if (own) out[row_of(tid)] = y - sy / (double)n;
+}
+
 // ------------------------------------------------------------ Alg. 1 step
 __global__ void k_sgd_propose(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
                               const double* __restrict__ h, int64_t E, double alpha,
@@ -316,10 +738,48 @@ struct Sgd {
     const int32_t *rpG, *colG, *rpP, *colP, *eoe, *eu, *ev;
     double *wG, *dG, *wPent, *dP, *w, *dw, *prop, *s1, *S, *h, *t1, *t2;
     double *y, *r, *z, *p, *q, *part, *sc;
+    unsigned long long* words;  // slots and z of the resident solve
+    int32_t* status;
+    double* b0;  // L_G h_0
+    bool resident;
     hipStream_t st;
     int cg_max;
     double cg_tol;
     int64_t cg_iters_max;
+
+    void take_resident(Arena& ws) {
+        words = ws.take<unsigned long long>(res_words(n));
+        status = reinterpret_cast<int32_t*>(sc + SC_STATUS);
+        b0 = ws.take<double>(n + 1);
+        t2 = ws.take<double>(n + 1);
+        resident = false;
+    }
+    // whether the solves on the current P run in one launch each
+    int plan_resident() {
+        resident = n > 0 && n <= kResN && nnzP <= kResNnz;
+        if (resident) {
+            int dev = 0, cus = 0, per_cu = 0;
+            GR_HIP(hipGetDevice(&dev));
+            GR_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+            GR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &per_cu, (const void*)k_cg_resident, kResThreads, 0));
+            resident = (int64_t)cus * per_cu >= kResBlocks;
+        }
+        return GR_OK;
+    }
+    int solve_resident(const double* b, double* out) {
+        GR_HIP(hipMemsetAsync(words, 0xff, sizeof(unsigned long long) * res_words(n), st));
+        const int32_t *rpv = rpP, *cv = colP;
+        const double *wv = wPent, *dv = dP;
+        int32_t nn = (int32_t)n, cm = cg_max;
+        double tol2 = cg_tol * cg_tol;
+        void* args[] = {(void*)&rpv, (void*)&cv, (void*)&wv, (void*)&dv, (void*)&nn, (void*)&b,
+                        (void*)&out, (void*)&words, (void*)&status, (void*)&cm,
+                        (void*)&tol2};
+        GR_HIP(hipLaunchCooperativeKernel((const void*)k_cg_resident, dim3(kResBlocks),
+                                          dim3(kResThreads), args, 0, st));
+        return GR_OK;
+    }
 
     int dot(const double* x, const double* yv, int64_t m, int slot) {
         hipLaunchKernelGGL(k_dot_part, dim3(kRedBlocks), dim3(kS), 0, st, x, yv, m, part);
@@ -391,18 +851,35 @@ struct Sgd {
         GR_HIP(hipMemcpyAsync(out, y, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
         return centre(out);
     }
-    // h_t: t generalised power iterations h <- L_P^+ L_G h from the centred
-    // h_0, normalised to h^T L_P h = 1 (into h); lambda_n = h^T L_G h
-    // (device slot SC_LAMN and *lam)
-    int power_vector(uint64_t seed, int t_iters, double* lam) {
-        const unsigned nb = blocks_for(n, kS);
-        hipLaunchKernelGGL(k_init_h, dim3(nb), dim3(kS), 0, st, n, seed, h);
+    // b0 = L_G h_0 (the same for every power vector of one seed), h_0 centred
+    int start_power(uint64_t seed) {
+        hipLaunchKernelGGL(k_init_h, dim3(blocks_for(n, kS)), dim3(kS), 0, st, n, seed, h);
         GR_LAUNCHED("h0");
         GR_TRY(centre(h));
+        return lapG(h, b0);
+    }
+    // h = L_P^+ b, b centred first
+    int solve_centred(double* b, double* out) {
+        if (resident) return solve_resident(b, out);
+        GR_HIP(hipMemcpyAsync(t1, b, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
+        GR_TRY(centre(t1));
+        return solve(t1, out);
+    }
+    // h_t: t generalised power iterations h <- L_P^+ L_G h from the centred
+    // h_0 (after start_power), normalised to h^T L_P h = 1 (into h);
+    // lambda_n = h^T L_G h (device slot SC_LAMN and *lam); *lam1, if wanted,
+    // is the slot SC_LAM1 as it was before
+    int power_vector(uint64_t seed, int t_iters, double* lam, double* lam1 = nullptr) {
+        const unsigned nb = blocks_for(n, kS);
+        if (resident) GR_HIP(hipMemsetAsync(status, 0, sizeof(int32_t) * RES_WORDS, st));
+        if (t_iters <= 0) {
+            hipLaunchKernelGGL(k_init_h, dim3(nb), dim3(kS), 0, st, n, seed, h);
+            GR_LAUNCHED("h0");
+            GR_TRY(centre(h));
+        }
         for (int t = 0; t < t_iters; ++t) {
-            GR_TRY(lapG(h, t1));
-            GR_TRY(centre(t1));
-            GR_TRY(solve(t1, h));
+            if (t > 0) GR_TRY(lapG(h, t2));
+            GR_TRY(solve_centred(t > 0 ? t2 : b0, h));
         }
         GR_TRY(lapP(h, t1));
         GR_TRY(dot(h, t1, n, SC_HLH));
@@ -410,7 +887,23 @@ struct Sgd {
         GR_LAUNCHED("normalise");
         GR_TRY(lapG(h, t1));
         GR_TRY(dot(h, t1, n, SC_LAMN));
-        *lam = read(SC_LAMN);
+        // one read back: the scalars and the solves' status behind them
+        double hs[SC_WORDS];
+        GR_HIP(hipMemcpyAsync(hs, sc, sizeof(hs), hipMemcpyDeviceToHost, st));
+        GR_HIP(hipStreamSynchronize(st));
+        *lam = hs[SC_LAMN];
+        if (lam1) *lam1 = hs[SC_LAM1];
+        if (resident) {
+            int32_t state[RES_WORDS];
+            memcpy(state, hs + SC_STATUS, sizeof(state));
+            if (state[RES_FLAGS] & RES_UNFIT) {  // some workgroup's rows do not fit: by launches
+                resident = false;
+                return power_vector(seed, t_iters, lam, lam1);
+            }
+            if (state[RES_FLAGS] & RES_DIVERGED) return set_error(GR_EHIP, "CG diverged");
+            if (state[RES_FLAGS] & RES_TIMEOUT) return set_error(GR_EHIP, "CG wait timed out");
+            cg_iters_max = std::max<int64_t>(cg_iters_max, state[RES_ITERS]);
+        }
         if (!(*lam == *lam)) return set_error(GR_EHIP, "lambda_n is not finite");
         return GR_OK;
     }
@@ -436,7 +929,7 @@ struct Sgd {
 
 size_t sgd_workspace(int64_t n, int64_t nnzG, int64_t nnzP, int64_t E) {
     size_t b = 8 * ((size_t)nnzG + (size_t)nnzP + 16 * (size_t)(n + 1) + 4 * (size_t)(E + 1)) +
-               8 * (kRedBlocks + 64) + 32 * 256;
+               8 * (kRedBlocks + 64) + 32 * 256 + 8 * (res_words(n) + 2 * ((size_t)n + 64));
     return b + b / 16 + (1u << 20);
 }
 
@@ -470,7 +963,6 @@ int sgd_scale(const gr_graph* G, const gr_graph* P, const int32_t* eoe, int64_t 
     s.S = ws.take<double>(n + 1);
     s.h = ws.take<double>(n + 1);
     s.t1 = ws.take<double>(n + 1);
-    s.t2 = ws.take<double>(n + 1);
     s.y = ws.take<double>(n + 1);
     s.r = ws.take<double>(n + 1);
     s.z = ws.take<double>(n + 1);
@@ -478,7 +970,9 @@ int sgd_scale(const gr_graph* G, const gr_graph* P, const int32_t* eoe, int64_t 
     s.q = ws.take<double>(n + 1);
     s.part = ws.take<double>(kRedBlocks + 1);
     s.sc = ws.take<double>(32);
+    s.take_resident(ws);
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (sgd)");
+    GR_TRY(s.plan_resident());
     const unsigned eb = blocks_for(E, kS);
     GR_HIP(hipMemsetAsync(s.sc, 0, sizeof(double) * 32, st));
     GR_HIP(hipMemsetAsync(s.dw, 0, sizeof(double) * (E + 1), st));
@@ -492,11 +986,11 @@ int sgd_scale(const gr_graph* G, const gr_graph* P, const int32_t* eoe, int64_t 
     GR_TRY(s.dot(s.w, nullptr, E, SC_SUMW0));
     const double delta = pow(prm->delta_bar, 1.0 / (double)prm->k_max);
     rep->iterations = 0;
-    rep->lambda_1[0] = s.read(SC_LAM1);
+    GR_TRY(s.start_power(prm->seed));
     double lam_prev = 0.0;
     for (int k = 0; k < prm->k_max && k < GR_SGD_MAX_ITER; ++k) {
         double lam = 0.0;
-        GR_TRY(s.power_vector(prm->seed, prm->t, &lam));
+        GR_TRY(s.power_vector(prm->seed, prm->t, &lam, &rep->lambda_1[k]));
         rep->lambda_n[k] = lam;
         if (k == 0) {
             hipLaunchKernelGGL(k_copy_scalar, dim3(1), dim3(1), 0, st, s.sc, (int)SC_LAMN,
@@ -533,9 +1027,9 @@ int sgd_scale(const gr_graph* G, const gr_graph* P, const int32_t* eoe, int64_t 
         hipLaunchKernelGGL(k_update_eta, dim3(1), dim3(1), 0, st, s.sc);
         GR_LAUNCHED("eta update");
         GR_TRY(s.lambda1());
-        rep->lambda_1[k + 1] = s.read(SC_LAM1);
         rep->iterations = k + 1;
     }
+    rep->lambda_1[rep->iterations] = s.read(SC_LAM1);
     rep->cg_iterations_max = (int32_t)s.cg_iters_max;
     return GR_OK;
 }
@@ -839,7 +1333,7 @@ size_t sparsify_workspace(int64_t n, int64_t nnz) {
                + 16 * N + 8 * E                     // forest state, counts
                + 8 * E + 2 * 12 * E                 // criticality, sort keys and values
                + 4 * N + 4 * E                      // subgraph counts and edge ranks
-               + 2 * 256 * 4 * (M / 2048 + 1) + M / 32 + 512 * 1024 + 8 * 4096;
+               + 2 * 256 * 4 * (M / 2048 + 1) + M / 32 + 512 * 1024 + 8 * 4096 + 8 * (res_words(n) + 2 * ((size_t)n + 64));
     return b + b / 8 + (2u << 20);
 }
 
@@ -891,6 +1385,7 @@ int sparsify(const gr_graph* g, const gr_sparsify_params* prm, int32_t* keep, do
     s.q = ws.take<double>(n + 1);
     s.part = ws.take<double>(kRedBlocks + 1);
     s.sc = ws.take<double>(32);
+    s.take_resident(ws);
     double* crit = ws.take<double>(E + 1);
     uint64_t* k0 = ws.take<uint64_t>(E + 1);
     uint32_t* v0 = ws.take<uint32_t>(E + 1);
@@ -909,6 +1404,7 @@ int sparsify(const gr_graph* g, const gr_sparsify_params* prm, int32_t* keep, do
         GR_TRY(subgraph(g, eoe, keep, E, nullptr, nullptr, prp, pcol, pw, nullptr, nullptr,
                         nullptr, &pnnz, &pedges, ws, st));
         s.nnzP = pnnz;
+        GR_TRY(s.plan_resident());
         hipLaunchKernelGGL(k_promote, dim3(blocks_for(pnnz, kS)), dim3(kS), 0, st, (const float*)pw,
                            pnnz, s.wPent);
         GR_LAUNCHED("promote P");
@@ -916,6 +1412,7 @@ int sparsify(const gr_graph* g, const gr_sparsify_params* prm, int32_t* keep, do
                            (const double*)s.wPent, n, s.dP);
         GR_LAUNCHED("d_P");
         double lam = 0.0;
+        if (round == 0) GR_TRY(s.start_power(prm->seed));
         GR_TRY(s.power_vector(prm->seed, prm->t, &lam));
         if (rep->n_lambda < GR_SPARSIFY_MAX_ROUNDS + 1) rep->lambda_n[rep->n_lambda++] = lam;
         rep->edges = pedges;
