@@ -33,95 +33,177 @@ constexpr int kMaxP = 64;  // widest block (columns)
 constexpr int kGramRows = 32;
 constexpr int kRowBlocks = 128;
 constexpr int kJacobiThreads = 1024;
+// Steps of the spectral bound: the filter's degree falls with the root of the
+// bound, and where hubs dominate 2 max degree is almost twice the largest
+// eigenvalue (13,000-node power law: 0.501 of it; the bound is 0.608, 0.555,
+// 0.537, 0.527, 0.522, 0.518 of it after 1 to 6 steps; 725 products per
+// solve became 509).
+constexpr int kBoundSteps = 6;
 
-// Y[:, 0:p] = L X[:, 0:p] for row-major blocks of stride ld.  Every row is
-// cut into pieces of ep consecutive entries (ep >= the mean degree, so that
-// there are at most 2n pieces, and a hub row spreads over many threads): the
-// first kernel writes each piece's partial sums, `lanes` threads (a power of
-// two >= p) per piece, one column each; the second adds a row's pieces in
-// order and applies the diagonal.  Fixed order: deterministic.
-__global__ void __launch_bounds__(kE) k_spmm_pieces(const int32_t* __restrict__ rp,
-                                                    const int32_t* __restrict__ col,
-                                                    const float* __restrict__ w,
-                                                    const int32_t* __restrict__ ppos,
-                                                    const int32_t* __restrict__ prow, int64_t npieces,
-                                                    int32_t ep, int p, int ld, int lanes,
-                                                    const double* __restrict__ X,
-                                                    const double* __restrict__ sc,
-                                                    double* __restrict__ part) {
-    const int64_t t = (int64_t)blockIdx.x * kE + threadIdx.x;
-    const int64_t k = t / lanes;
-    const int c = (int)(t % lanes);
-    if (k >= npieces || c >= p) return;
-    const int32_t v = prow[k];
-    const int32_t e0 = rp[v] + (int32_t)(k - ppos[v]) * ep;
-    const int32_t e1 = min(e0 + ep, rp[v + 1]);
-    double s = 0.0;
-    int32_t e = e0;
-    for (; e + 4 <= e1; e += 4) {  // four gathers in flight, summed in entry order
-        double xv[4], wv[4];
-        int32_t j[4];
+// Y[:, 0:p] = L X[:, 0:p] for row-major blocks of stride ld, or a Chebyshev
+// step with it.  Bound by the gathers of X's rows, which stay in L2 on
+// reduced graphs (13,000 nodes, 2.56M entries, p = 20: 410 MB gathered per
+// product).  A wave takes a row: `cw` lanes hold one entry's columns (two
+// each, as one 16-byte load, where p, ld and the arrays allow it), so that
+// 64 / cw entries ride in one load.  A lane per column, 32 lanes per row
+// piece, left 12 of 32 lanes idle at p = 20, and a second launch added the
+// pieces: 83 us with the Chebyshev step, here 33 us, 12 TB/s of gathers out
+// of L2.  More loads in flight per lane cost waves (8: 37 us), and loading
+// the entries past the caches costs more than it spares X in L2 (45 us).
+// Rows above kLapLong entries take a workgroup each, first in the grid, so
+// that hubs do not end it.  The slots' sums are added in slot order: the
+// result depends on p alone.
+constexpr int kLapThreads = 512;
+constexpr int kLapWaves = kLapThreads / kWave;
+constexpr int kLapU = 4;
+constexpr int32_t kLapLong = 512;
+
+// what the product becomes: L X, or the Chebyshev step 2 (L X - c X) / e - Z
+// (Z read and written in place)
+enum { LAP_PLAIN = 0, LAP_CHEB };
+
+struct LapStep {
+    int mode;
+    double c, e;
+};
+
+template <bool PAIR>
+__global__ void __launch_bounds__(kLapThreads) k_lap_block(
+    const int32_t* __restrict__ rp, const int32_t* __restrict__ col, const float* __restrict__ w,
+    const int32_t* __restrict__ long_rows, int32_t n_long, int64_t n, int p, int ld, int cw,
+    const double* __restrict__ X, const double* __restrict__ d, const double* __restrict__ sc,
+    LapStep step, double* __restrict__ Y) {
+    constexpr int C = PAIR ? 2 : 1;
+    __shared__ double sums[kLapWaves][kWave * C];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const bool whole = (int32_t)blockIdx.x < n_long;  // a row for the whole workgroup
+    const int64_t v = whole ? long_rows[blockIdx.x]
+                            : ((int64_t)blockIdx.x - n_long) * kLapWaves + wid;
+    if (!whole && v >= n) return;
+    const int32_t e0 = __builtin_amdgcn_readfirstlane(rp[v]);
+    const int32_t e1 = __builtin_amdgcn_readfirstlane(rp[v + 1]);
+    if (!whole && e1 - e0 > kLapLong) return;
+    const int slots = kWave / cw;
+    const int slot = lane / cw, cl = lane - slot * cw;
+    const bool active = slot < slots;
+    const int stride = whole ? slots * kLapWaves : slots;
+    const int first = whole ? wid * slots : 0;
+    const double* const Xc = X + cl * C;
+    double s[C];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            wv[u] = (double)w[e + u];
-            j[u] = col[e + u];
-            xv[u] = X[(int64_t)j[u] * ld + c];
+    for (int q = 0; q < C; ++q) s[q] = 0.0;
+    for (int32_t b = e0 + first; b < e1; b += kLapU * stride) {  // wave-uniform
+        int32_t j[kLapU];
+        float wv[kLapU];
+#pragma unroll
+        for (int u = 0; u < kLapU; ++u) {
+            const int32_t e = min(b + u * stride + (active ? slot : 0), e1 - 1);
+            j[u] = col[e];
+            wv[u] = w[e];
         }
-        if (sc) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) xv[u] *= sc[j[u]];
-        }
+        for (int u = 0; u < kLapU; ++u) asm volatile("" : "+v"(j[u]));
+        double x[kLapU][C];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s = fma(wv[u], xv[u], s);
+        for (int u = 0; u < kLapU; ++u)
+            if (u == 0 || b + u * stride < e1) {  // wave-uniform
+                const double* at = Xc + (int64_t)j[u] * ld;
+                if constexpr (PAIR) {
+                    const double2 t = *reinterpret_cast<const double2*>(at);
+                    x[u][0] = t.x;
+                    x[u][1] = t.y;
+                } else {
+                    x[u][0] = cl < p ? *at : 0.0;
+                }
+            }
+#pragma unroll
+        for (int u = 0; u < kLapU; ++u)
+            if (b + u * stride + slot < e1) {
+                const double f = sc ? sc[j[u]] : 1.0;
+#pragma unroll
+                for (int q = 0; q < C; ++q) s[q] = fma((double)wv[u], sc ? x[u][q] * f : x[u][q], s[q]);
+            }
     }
-    for (; e < e1; ++e) {
-        const int32_t j = col[e];
-        const double x = sc ? X[(int64_t)j * ld + c] * sc[j] : X[(int64_t)j * ld + c];
-        s = fma((double)w[e], x, s);
+#pragma unroll
+    for (int q = 0; q < C; ++q) sums[wid][lane * C + q] = active ? s[q] : 0.0;
+    if (whole) {
+        __syncthreads();
+        if (wid > 0) return;
     }
-    part[k * p + c] = s;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (lane >= cw) return;
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+        const int c = lane * C + q;
+        if (c >= p) continue;
+        double t = 0.0;
+        for (int k = 0; k < (whole ? kLapWaves : 1); ++k)
+            for (int l = 0; l < slots; ++l) t += sums[whole ? k : wid][(l * cw + lane) * C + q];
+        const double x = X[v * ld + c];
+        const double y = sc ? sc[v] * (d[v] * (sc[v] * x) - t) : d[v] * x - t;
+        double* at = Y + v * ld + c;
+        *at = step.mode == LAP_PLAIN ? y : 2.0 * ((y - step.c * x) / step.e) - *at;
+    }
 }
 
-__global__ void __launch_bounds__(kE) k_spmm_rows(const int32_t* __restrict__ ppos,
-                                                  const double* __restrict__ d, int64_t n, int p,
-                                                  int ld, int lanes,
-                                                  const double* __restrict__ part,
-                                                  const double* __restrict__ X,
-                                                  const double* __restrict__ sc,
-                                                  double* __restrict__ Y) {
-    const int64_t t = (int64_t)blockIdx.x * kE + threadIdx.x;
-    const int64_t v = t / lanes;
-    const int c = (int)(t % lanes);
-    if (v >= n || c >= p) return;
-    double s = 0.0;
-    for (int32_t k = ppos[v]; k < ppos[v + 1]; ++k) s += part[(int64_t)k * p + c];
-    if (sc)  // S L S X with S = diag(sc)
-        Y[v * ld + c] = sc[v] * (d[v] * (sc[v] * X[v * ld + c]) - s);
-    else
-        Y[v * ld + c] = d[v] * X[v * ld + c] - s;
-}
-
-// pieces of every row, and the row of every piece
-__global__ void k_piece_counts_e(const int32_t* __restrict__ rp, int64_t n, int32_t ep,
-                                 int32_t* __restrict__ cnt) {
+// flags of the rows above kLapLong, and their list from the flags' scan
+__global__ void k_lap_long_flags(const int32_t* __restrict__ rp, int64_t n, int32_t* __restrict__ f) {
     const int64_t v = (int64_t)blockIdx.x * kE + threadIdx.x;
-    if (v < n) cnt[v] = (rp[v + 1] - rp[v] + ep - 1) / ep;
+    if (v < n) f[v] = rp[v + 1] - rp[v] > kLapLong ? 1 : 0;
 }
 
-__global__ void k_piece_rows(const int32_t* __restrict__ ppos, int64_t n, int32_t* __restrict__ prow) {
+__global__ void k_lap_long_list(const int32_t* __restrict__ rp, const int32_t* __restrict__ pos,
+                                int64_t n, int32_t* __restrict__ list) {
     const int64_t v = (int64_t)blockIdx.x * kE + threadIdx.x;
-    if (v >= n) return;
-    for (int32_t k = ppos[v]; k < ppos[v + 1]; ++k) prow[k] = (int32_t)v;
+    if (v < n && rp[v + 1] - rp[v] > kLapLong) list[pos[v]] = (int32_t)v;
 }
 
-// Chebyshev step on contiguous blocks: Z = (2/e) (L Y - c Y) - Z, or
-// (1/e) (L Y - c Y) for the first step
-__global__ void k_cheb(const double* __restrict__ LY, const double* __restrict__ Y,
-                       double* __restrict__ Z, int64_t cnt, double c, double e, int first) {
+// The first Chebyshev step from L X at hand: Z = (L X - c X) / e
+__global__ void k_cheb_first(const double* __restrict__ LX, const double* __restrict__ X,
+                             double* __restrict__ Z, int64_t cnt, double c, double e) {
     int64_t i = (int64_t)blockIdx.x * kE + threadIdx.x;
-    if (i >= cnt) return;
-    double t = (LY[i] - c * Y[i]) / e;
-    Z[i] = first ? t : 2.0 * t - Z[i];
+    if (i < cnt) Z[i] = (LX[i] - c * X[i]) / e;
+}
+
+// One step of the Collatz-Wielandt bound of Q = D + A, whose spectral radius
+// is at least L's: for every positive x, rho(Q) <= max_v (Q x)_v / x_v.
+// y = Q x / (2 max degree), a wave per row; top = the largest ratio, as the
+// bits of a positive double (a row with entries whose x has vanished gives
+// the plain bound 2 max degree).  x0: the degrees.
+__global__ void __launch_bounds__(kE) k_bound_step(const int32_t* __restrict__ rp,
+                                                   const int32_t* __restrict__ col,
+                                                   const float* __restrict__ w,
+                                                   const double* __restrict__ d, int64_t n,
+                                                   const double* __restrict__ dmax,
+                                                   const double* __restrict__ x,
+                                                   double* __restrict__ y,
+                                                   unsigned long long* __restrict__ top) {
+    __shared__ double wtop[kE / kWave];
+    const int64_t v = ((int64_t)blockIdx.x * kE + threadIdx.x) / kWave;
+    const int l = threadIdx.x & (kWave - 1);
+    const double b = 2.0 * *dmax;
+    double ratio = 0.0;
+    if (v < n) {
+        double s = 0.0;
+        for (int32_t e = rp[v] + l; e < rp[v + 1]; e += kWave) s = fma((double)w[e], x[col[e]], s);
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) s += __shfl_xor(s, off, kWave);
+        s = fma(d[v], x[v], s);
+        if (l == 0) y[v] = b > 0.0 ? s / b : 0.0;
+        ratio = d[v] > 0.0 ? (x[v] > 0.0 ? fmin(s / x[v], b) : b) : 0.0;
+    }
+    if (l == 0) wtop[threadIdx.x / kWave] = ratio;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kE / kWave; ++k) ratio = fmax(ratio, wtop[k]);
+        // read first: same-address atomics serialise, and most blocks have
+        // nothing to add
+        const unsigned long long r = (unsigned long long)__double_as_longlong(ratio);
+        if (r > __hip_atomic_load(top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(top, r);
+    }
 }
 
 // a wave per row (hub rows hold thousands of entries), fixed reduction tree
@@ -171,6 +253,20 @@ __global__ void k_fix_zero_cols(const double* __restrict__ G, int64_t n, int p, 
     if (!(gc > 1e-200 * gmax)) X[v * ld + c] = block_rand(seed, v, c);
 }
 
+// The sum over a block's threads of the same column, kE / p threads each
+// (thread t has column t % p of row t / p): column c's sum to part[c].
+__device__ inline void block_column_sums(double s, int p, double* __restrict__ part) {
+    __shared__ double red[kE];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    const int c = threadIdx.x;
+    if (c < p) {
+        double t = 0.0;
+        for (int r = 0; r < kE / p; ++r) t += red[r * p + c];
+        part[c] = t;
+    }
+}
+
 // per-block partial column sums of X[:, 0:p] (stride ld), weighted by q
 // when q is given (the products q^T X)
 __global__ void __launch_bounds__(kE) k_colsum_part(const double* __restrict__ X, int64_t n, int p,
@@ -178,14 +274,15 @@ __global__ void __launch_bounds__(kE) k_colsum_part(const double* __restrict__ X
                                                     double* __restrict__ part) {
     const int64_t R = (n + gridDim.x - 1) / gridDim.x;
     const int64_t lo = (int64_t)blockIdx.x * R, hi = min(n, lo + R);
-    for (int c = threadIdx.x; c < p; c += kE) {
-        double s = 0.0;
+    const int c = threadIdx.x % p, r = threadIdx.x / p, rows = kE / p;
+    double s = 0.0;
+    if (r < rows) {
         if (q)
-            for (int64_t v = lo; v < hi; ++v) s = fma(q[v], X[v * ld + c], s);
+            for (int64_t v = lo + r; v < hi; v += rows) s = fma(q[v], X[v * ld + c], s);
         else
-            for (int64_t v = lo; v < hi; ++v) s += X[v * ld + c];
-        part[(int64_t)blockIdx.x * p + c] = s;
+            for (int64_t v = lo + r; v < hi; v += rows) s += X[v * ld + c];
     }
+    block_column_sums(s, p, part + (int64_t)blockIdx.x * p);
 }
 
 // s = sum over b of part[b * stride + idx], in b order, eight loads in flight
@@ -460,14 +557,16 @@ __global__ void __launch_bounds__(kE) k_resid_part(const double* __restrict__ LX
                                                    int m, int ld, double* __restrict__ part) {
     const int64_t R = (n + gridDim.x - 1) / gridDim.x;
     const int64_t lo = (int64_t)blockIdx.x * R, hi = min(n, lo + R);
-    for (int c = threadIdx.x; c < m; c += kE) {
-        double s = 0.0;
-        for (int64_t v = lo; v < hi; ++v) {
-            double r = LX[v * ld + c] - theta[c] * X[v * ld + c];
+    const int c = threadIdx.x % m, rows = kE / m;
+    double s = 0.0;
+    if ((int)threadIdx.x / m < rows) {
+        const double th = theta[c];
+        for (int64_t v = lo + threadIdx.x / m; v < hi; v += rows) {
+            const double r = LX[v * ld + c] - th * X[v * ld + c];
             s = fma(r, r, s);
         }
-        part[(int64_t)blockIdx.x * m + c] = s;
     }
+    block_column_sums(s, m, part + (int64_t)blockIdx.x * m);
 }
 
 __global__ void k_precond_resid(const double* __restrict__ LX, double* __restrict__ S,
@@ -515,10 +614,8 @@ struct Eig {
     int fix_round;
     double *d, *dinv, *S, *LS, *T, *U, *part, *G, *M, *theta, *cs, *res, *small;
     int* flag;
-    int32_t *ppos, *prow;  // row pieces of the Laplacian product
-    double* ppart;         // their partial sums [npieces][p]
-    int64_t npieces;
-    int32_t ep;            // entries per piece
+    int32_t* long_rows;  // rows above kLapLong entries
+    int32_t n_long;
     // generalised problem L u = lambda B u with B = diag(b) > 0: the solver
     // works on S L S (S = diag(b)^-1/2) in the complement of q = b^1/2,
     // its null vector; u = S v.  All three NULL for B = I.
@@ -526,24 +623,20 @@ struct Eig {
     const double* q = nullptr;   // b^1/2
     double* qq = nullptr;        // q^T q = sum of b (device scalar)
 
-    static int lanes_for(int p) {
-        int l = 1;
-        while (l < p) l <<= 1;
-        return l;
-    }
-    // B[:, 0:p] = L A[:, 0:p]
-    int spmm(const double* A, double* B, int p) {
-        const int lanes = lanes_for(p);
-        if (npieces > 0) {
-            hipLaunchKernelGGL(k_spmm_pieces, dim3(blocks_for(npieces * lanes, kE)), dim3(kE), 0, st,
-                               g->row_ptr, g->col, g->w, (const int32_t*)ppos, (const int32_t*)prow,
-                               npieces, ep, p, ld, lanes, A, sc, ppart);
-            GR_LAUNCHED("spmm pieces");
-        }
-        hipLaunchKernelGGL(k_spmm_rows, dim3(blocks_for(n * lanes, kE)), dim3(kE), 0, st,
-                           (const int32_t*)ppos, (const double*)d, n, p, ld, lanes,
-                           (const double*)ppart, A, sc, B);
-        GR_LAUNCHED("spmm rows");
+    // B[:, 0:p] = L A[:, 0:p], or the Chebyshev step
+    int spmm(const double* A, double* B, int p, LapStep step = LapStep{LAP_PLAIN, 0.0, 1.0}) {
+        const unsigned nb = (unsigned)n_long + blocks_for(n, kLapWaves);
+        const bool pair = p % 2 == 0 && ld % 2 == 0 &&
+                          ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15) == 0;
+        if (pair)
+            hipLaunchKernelGGL(k_lap_block<true>, dim3(nb), dim3(kLapThreads), 0, st, g->row_ptr,
+                               g->col, g->w, (const int32_t*)long_rows, n_long, n, p, ld, p / 2, A,
+                               (const double*)d, sc, step, B);
+        else
+            hipLaunchKernelGGL(k_lap_block<false>, dim3(nb), dim3(kLapThreads), 0, st, g->row_ptr,
+                               g->col, g->w, (const int32_t*)long_rows, n_long, n, p, ld, p, A,
+                               (const double*)d, sc, step, B);
+        GR_LAUNCHED("Laplacian product");
         return GR_OK;
     }
     int project(double* A, int p) {
@@ -634,7 +727,7 @@ size_t eig_workspace(int64_t n, int32_t n_eig) {
 }
 
 // Chebyshev-filtered subspace iteration; block m, ld = m
-static int run_chebyshev(Eig& s, int n_eig, int m, double b, double tol, int max_iter, int degree,
+static int run_chebyshev(Eig& s, int n_eig, int m, double b, double bf, double tol, int max_iter, int degree,
                          std::vector<double>& th, double& worst, int& it) {
     const int64_t n = s.n;
     const int64_t cnt = n * m;
@@ -663,27 +756,24 @@ static int run_chebyshev(Eig& s, int n_eig, int m, double b, double tol, int max
         worst = 0.0;
         for (int i = 0; i < n_eig && i < m; ++i) worst = fmax(worst, sqrt(fmax(rs[i], 0.0)));
         if (worst <= tol * b || m >= n - 1 || it >= max_iter) break;
-        // filter on [a, b], a = the largest Ritz value:
+        // filter on [a, bf], a = the largest Ritz value:
         // Z_0 = X, Z_1 = (L X - c X)/e, Z_j = 2 (L Z_{j-1} - c Z_{j-1})/e - Z_{j-2}
         const double a = th[m - 1];
-        const double c = 0.5 * (b + a), e = 0.5 * (b - a);
-        if (!(e > 0.0)) break;  // the block already spans [0, b]
+        const double c = 0.5 * (bf + a), e = 0.5 * (bf - a);
+        if (!(e > 0.0)) break;  // the block already spans [0, bf]
         // cap the degree so that the largest amplification (at lambda = 0,
-        // T_k((b + a) / (b - a))) stays below 1e6: the filtered block then
+        // T_k((bf + a) / (bf - a))) stays below 1e6: the filtered block then
         // has a condition number shifted Cholesky QR takes comfortably
         int deg = degree;
         const double per = acosh(fmax(c / e, 1.0));
         if (per > 0.0) deg = (int)fmin((double)degree, fmax(1.0, floor(acosh(1e6) / per)));
         double* Z0 = s.S;  // Z_{j-2}
         double* Z1 = s.T;  // Z_{j-1}
-        hipLaunchKernelGGL(k_cheb, dim3(blocks_for(cnt, kE)), dim3(kE), 0, st, (const double*)s.LS,
-                           (const double*)s.S, s.T, cnt, c, e, 1);
+        hipLaunchKernelGGL(k_cheb_first, dim3(blocks_for(cnt, kE)), dim3(kE), 0, st,
+                           (const double*)s.LS, (const double*)s.S, s.T, cnt, c, e);
         GR_LAUNCHED("cheb 1");
         for (int j = 2; j <= deg; ++j) {
-            GR_TRY(s.spmm(Z1, s.U, m));
-            hipLaunchKernelGGL(k_cheb, dim3(blocks_for(cnt, kE)), dim3(kE), 0, st, (const double*)s.U,
-                               (const double*)Z1, Z0, cnt, c, e, 0);
-            GR_LAUNCHED("cheb");
+            GR_TRY(s.spmm(Z1, Z0, m, LapStep{LAP_CHEB, c, e}));
             std::swap(Z0, Z1);
         }
         if (Z1 != s.S) std::swap(s.S, s.T);  // the filtered block into S
@@ -813,41 +903,35 @@ __global__ void __launch_bounds__(kE) k_gersh_rows(const int32_t* __restrict__ r
     if (l == 0) out[v] = sc[v] * (d[v] * sc[v] + s);
 }
 
-// degrees and row pieces of the Laplacian product of s.g for blocks of up
-// to maxp columns (d, dinv, ppos, prow, ppart taken from ws)
-static int setup_operator(Eig& s, int maxp, Arena& ws) {
+// degrees and the list of long rows of the Laplacian product of s.g (d,
+// dinv, long_rows taken from ws)
+static int setup_operator(Eig& s, Arena& ws) {
     const gr_graph* g = s.g;
     const int64_t n = g->n;
     hipStream_t st = s.st;
     s.d = ws.take<double>(n + 1);
     s.dinv = ws.take<double>(n + 1);
-    s.ppos = ws.take<int32_t>(n + 1);
-    s.prow = ws.take<int32_t>(2 * (size_t)n + 1);
-    s.ppart = ws.take<double>((2 * (size_t)n + 1) * maxp);
+    s.long_rows = ws.take<int32_t>(n + 1);
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (Laplacian product)");
     hipLaunchKernelGGL(k_degree_f64, dim3(blocks_for(n * kWave, kE)), dim3(kE), 0, st, g->row_ptr,
                        g->w, n, s.d, s.dinv);
     GR_LAUNCHED("degrees");
-    // row pieces of at least the mean degree: at most n + nnz / ep <= 2n
-    s.ep = (int32_t)std::max<int64_t>(64, (g->nnz + n - 1) / (n > 0 ? n : 1));
-    {
-        const size_t mark = ws.used;
-        int32_t* cnt = ws.take<int32_t>(n);
-        if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (eigen pieces)");
-        hipLaunchKernelGGL(k_piece_counts_e, dim3(blocks_for(n, kE)), dim3(kE), 0, st, g->row_ptr, n,
-                           s.ep, cnt);
-        GR_LAUNCHED("piece counts");
-        GR_TRY(scan_exclusive_i32(cnt, s.ppos, n, s.ppos + n, ws, st));
-        ws.used = mark;
-    }
-    hipLaunchKernelGGL(k_piece_rows, dim3(blocks_for(n, kE)), dim3(kE), 0, st, (const int32_t*)s.ppos,
-                       n, s.prow);
-    GR_LAUNCHED("piece rows");
-    int32_t np32 = 0;
-    GR_HIP(hipMemcpyAsync(&np32, s.ppos + n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    s.n_long = 0;
+    if (g->nnz <= kLapLong) return GR_OK;
+    const size_t mark = ws.used;
+    int32_t* flag = ws.take<int32_t>(n);
+    int32_t* pos = ws.take<int32_t>(n + 1);
+    if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (long rows)");
+    const unsigned nb = blocks_for(n, kE);
+    hipLaunchKernelGGL(k_lap_long_flags, dim3(nb), dim3(kE), 0, st, g->row_ptr, n, flag);
+    GR_LAUNCHED("long row flags");
+    GR_TRY(scan_exclusive_i32(flag, pos, n, pos + n, ws, st));
+    hipLaunchKernelGGL(k_lap_long_list, dim3(nb), dim3(kE), 0, st, g->row_ptr, (const int32_t*)pos,
+                       n, s.long_rows);
+    GR_LAUNCHED("long rows");
+    GR_HIP(hipMemcpyAsync(&s.n_long, pos + n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     GR_HIP(hipStreamSynchronize(st));
-    s.npieces = np32;
-    if (s.npieces > 2 * n) return set_error(GR_EINVAL, "row pieces exceed 2n");
+    ws.used = mark;
     return GR_OK;
 }
 
@@ -870,20 +954,37 @@ int laplacian_eigs(const gr_graph* g, const double* bdiag, int32_t n_eig, int32_
     s.theta = ws.take<double>(kMaxP);
     s.cs = ws.take<double>(kMaxP);
     s.res = ws.take<double>(kMaxP);
-    s.small = ws.take<double>(8);
+    s.small = ws.take<double>(2 + kBoundSteps);
     s.flag = ws.take<int>(4);
     double* bsc = bdiag ? ws.take<double>(n + 1) : nullptr;
     double* bq = bdiag ? ws.take<double>(n + 1) : nullptr;
     double* bqq = bdiag ? ws.take<double>(8) : nullptr;
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (eigen)");
     GR_HIP(hipMemsetAsync(s.flag, 0, sizeof(int) * 4, st));
-    GR_TRY(setup_operator(s, kMaxP, ws));
+    GR_TRY(setup_operator(s, ws));
     hipLaunchKernelGGL(k_deg_stats, dim3(1), dim3(kE), 0, st, (const double*)s.d, n, s.small);
     GR_LAUNCHED("degree stats");
-    double dstat[2] = {0.0, 0.0};
+    // a closer bound for the filter's interval (small[2 ..], one per step)
+    unsigned long long* tops = reinterpret_cast<unsigned long long*>(s.small + 2);
+    if (!bdiag) {
+        GR_HIP(hipMemsetAsync(tops, 0, sizeof(double) * kBoundSteps, st));
+        const double* x = s.d;
+        for (int k = 0; k < kBoundSteps; ++k) {
+            double* y = k % 2 ? s.U : s.T;
+            hipLaunchKernelGGL(k_bound_step, dim3(blocks_for(n * kWave, kE)), dim3(kE), 0, st,
+                               g->row_ptr, g->col, g->w, (const double*)s.d, n,
+                               (const double*)s.small, x, y, tops + k);
+            GR_LAUNCHED("spectral bound");
+            x = y;
+        }
+    }
+    double dstat[2 + kBoundSteps];
     GR_HIP(hipMemcpyAsync(dstat, s.small, sizeof(dstat), hipMemcpyDeviceToHost, st));
     GR_HIP(hipStreamSynchronize(st));
     double b = 2.0 * dstat[0] * (1.0 + 1e-12) + 1e-300;  // lambda_max <= 2 max degree
+    double bf = b;
+    if (!bdiag)
+        for (int k = 0; k < kBoundSteps; ++k) bf = fmin(bf, 1.01 * dstat[2 + k] + 1e-300);
     const double mean = dstat[1] / (double)n;
     if (bdiag) {  // the generalised problem: S L S in the complement of b^1/2
         hipLaunchKernelGGL(k_b_setup, dim3(blocks_for(n, kE)), dim3(kE), 0, st, bdiag,
@@ -909,6 +1010,7 @@ int laplacian_eigs(const gr_graph* g, const double* bdiag, int32_t n_eig, int32_
         GR_HIP(hipStreamSynchronize(st));
         if (fl[1]) return set_error(GR_EINVAL, "the diagonal of B must be positive and finite");
         b = gs[0] * (1.0 + 1e-12) + 1e-300;
+        bf = b;
         s.sc = bsc;
         s.q = bq;
         s.qq = bqq;
@@ -932,7 +1034,7 @@ int laplacian_eigs(const gr_graph* g, const double* bdiag, int32_t n_eig, int32_
         m = cheb_block(n_eig);
         if (m > n - 1) m = (int)(n - 1);
         s.ld = m;
-        GR_TRY(run_chebyshev(s, n_eig, m, b, tol, max_iter, degree, th, worst, it));
+        GR_TRY(run_chebyshev(s, n_eig, m, b, bf, tol, max_iter, degree, th, worst, it));
     }
     int flag = 0;
     GR_HIP(hipMemcpyAsync(&flag, s.flag, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -1027,7 +1129,7 @@ int jacobi_filter(const gr_graph* g, int32_t k, double* Y, const double* lam_hos
     s.n = n;
     s.st = st;
     s.ld = k;
-    GR_TRY(setup_operator(s, k, ws));
+    GR_TRY(setup_operator(s, ws));
     double* LY = ws.take<double>((size_t)n * k + 1);
     double* lam = lam_host ? ws.take<double>(k) : nullptr;
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (Jacobi filter)");
