@@ -6,6 +6,7 @@
 #include "gr_internal.hpp"
 #include "gr_device.hpp"
 
+#include <algorithm>
 #include <mutex>
 
 namespace gr {
@@ -136,90 +137,190 @@ int expand_weights(const int32_t* eoe, int64_t nnz, int64_t E, const float* wE, 
 // ------------------------------------------------------- Rayleigh quotients
 constexpr int kRqBlocks = 512;
 
-__device__ inline double block_sum_d(double v, double* sh) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    if ((threadIdx.x & (kWave - 1)) == 0) sh[threadIdx.x / kWave] = v;
-    __syncthreads();
-    double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < kA / kWave; ++w) t += sh[w];
-    __syncthreads();
-    return t;
+// Bound by the gathers of the edges' end rows (16 m bytes per edge, out of
+// L2 on reduced graphs).  cw lanes hold one edge's columns, two each as one
+// 16-byte load where m and U's alignment allow it, so that a wave's load
+// covers 64 / cw edges' whole rows; kRqU edges are in flight per lane.
+// (The column as a grid dimension read the edge list m times over, and a
+// thread per edge in the gradient touched a line per lane and column: 65 and
+// 57 us at 1.28M edges and m = 10; here 22 and 26 us, 10 and 9 TB/s with the
+// edge list.)
+constexpr int kRqThreads = 512;
+constexpr int kRqWaves = kRqThreads / kWave;
+constexpr int kRqU = 4;
+
+// columns cl C .. of row v
+template <int C>
+__device__ inline void rq_row(const double* __restrict__ U, int64_t v, int m, int cl, double* x) {
+    const double* at = U + v * m + cl * C;
+    if constexpr (C == 2) {
+        const double2 t = *reinterpret_cast<const double2*>(at);
+        x[0] = t.x;
+        x[1] = t.y;
+    } else {
+        x[0] = *at;
+    }
 }
 
-// grid (kRqBlocks, m): partial sums over edges (grid-stride) of
+// per block (grid-stride): partial sums over edges of
 //   num_i = sum_e w_e (u_pi - u_qi)^2   and, for B = D(w),
-//   den_i = sum_e w_e (u_pi^2 + u_qi^2)  (= u_i^T D u_i).
-__global__ void __launch_bounds__(kA) k_rq_edges(int64_t E, const int32_t* __restrict__ eu,
-                                                 const int32_t* __restrict__ ev,
-                                                 const double* __restrict__ w,
-                                                 const double* __restrict__ U, int32_t m, int mode,
-                                                 double* __restrict__ part_num,
-                                                 double* __restrict__ part_den) {
-    __shared__ double sh[kA / kWave];
-    const int i = blockIdx.y;
-    double num = 0.0, den = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * kA + threadIdx.x; e < E; e += (int64_t)gridDim.x * kA) {
-        double up = U[(int64_t)eu[e] * m + i], uq = U[(int64_t)ev[e] * m + i];
-        double df = up - uq;
-        num = fma(w[e] * df, df, num);
-        if (mode == GR_RQ_DEGREE) den = fma(w[e], up * up + uq * uq, den);
+//   den_i = sum_e w_e (u_pi^2 + u_qi^2)  (= u_i^T D u_i),
+// for B = I the partial sums over nodes of den_i = u_i^T u_i
+template <int C>
+__global__ void __launch_bounds__(kRqThreads) k_rq_sums(int64_t n, int64_t E,
+                                                        const int32_t* __restrict__ eu,
+                                                        const int32_t* __restrict__ ev,
+                                                        const double* __restrict__ w,
+                                                        const double* __restrict__ U, int32_t m,
+                                                        int cw, int mode,
+                                                        double* __restrict__ part_num,
+                                                        double* __restrict__ part_den) {
+    __shared__ double red[2][kRqWaves][kWave * C];
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int slots = kWave / cw, slot = lane / cw, cl = lane - slot * cw;
+    const bool active = slot < slots;
+    const int64_t wave = (int64_t)blockIdx.x * kRqWaves + wid;
+    const int64_t step = (int64_t)gridDim.x * kRqWaves * slots * kRqU;
+    double num[C], den[C];
+#pragma unroll
+    for (int q = 0; q < C; ++q) num[q] = den[q] = 0.0;
+    if (active)
+        for (int64_t b = wave * slots * kRqU + slot; b < E; b += step) {
+            int32_t p[kRqU], q[kRqU];
+            double we[kRqU], xp[kRqU][C], xq[kRqU][C];
+#pragma unroll
+            for (int u = 0; u < kRqU; ++u) {
+                const int64_t e = b + u * slots < E ? b + u * slots : b;
+                p[u] = eu[e];
+                q[u] = ev[e];
+                we[u] = w[e];
+            }
+#pragma unroll
+            for (int u = 0; u < kRqU; ++u) {
+                rq_row<C>(U, p[u], m, cl, xp[u]);
+                rq_row<C>(U, q[u], m, cl, xq[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kRqU; ++u)
+                if (b + u * slots < E) {
+#pragma unroll
+                    for (int k = 0; k < C; ++k) {
+                        const double df = xp[u][k] - xq[u][k];
+                        num[k] = fma(we[u] * df, df, num[k]);
+                        if (mode == GR_RQ_DEGREE)
+                            den[k] = fma(we[u], xp[u][k] * xp[u][k] + xq[u][k] * xq[u][k], den[k]);
+                    }
+                }
+        }
+    if (active && mode == GR_RQ_IDENTITY)
+        for (int64_t v = wave * slots + slot; v < n; v += (int64_t)gridDim.x * kRqWaves * slots) {
+            double x[C];
+            rq_row<C>(U, v, m, cl, x);
+#pragma unroll
+            for (int k = 0; k < C; ++k) den[k] = fma(x[k], x[k], den[k]);
+        }
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        red[0][wid][lane * C + k] = num[k];
+        red[1][wid][lane * C + k] = den[k];
     }
-    num = block_sum_d(num, sh);
-    den = block_sum_d(den, sh);
-    if (threadIdx.x == 0) {
-        part_num[(int64_t)i * gridDim.x + blockIdx.x] = num;
-        part_den[(int64_t)i * gridDim.x + blockIdx.x] = den;
+    __syncthreads();
+    // column t % m of the sums t / m (num, den): slots in order, then waves
+    const int t = threadIdx.x;
+    if (t < 2 * m) {
+        const int c = t % m;
+        double s = 0.0;
+        for (int k = 0; k < kRqWaves; ++k) {
+            double x = 0.0;
+            for (int l = 0; l < slots; ++l) x += red[t / m][k][l * cw * C + c];
+            s += x;
+        }
+        (t < m ? part_num : part_den)[(int64_t)c * gridDim.x + blockIdx.x] = s;
     }
 }
 
-// grid (kRqBlocks, m): partial sums of u_i^T u_i over nodes (B = I)
-__global__ void __launch_bounds__(kA) k_rq_nodes(int64_t n, const double* __restrict__ U, int32_t m,
-                                                 double* __restrict__ part_den) {
-    __shared__ double sh[kA / kWave];
-    const int i = blockIdx.y;
-    double den = 0.0;
-    for (int64_t v = (int64_t)blockIdx.x * kA + threadIdx.x; v < n; v += (int64_t)gridDim.x * kA) {
-        double u = U[v * m + i];
-        den = fma(u, u, den);
-    }
-    den = block_sum_d(den, sh);
-    if (threadIdx.x == 0) part_den[(int64_t)i * gridDim.x + blockIdx.x] = den;
-}
-
-__global__ void k_rq_final(const double* __restrict__ part_num, const double* __restrict__ part_den,
-                           int nb, int32_t m, double* __restrict__ R, double* __restrict__ den_out) {
-    int i = threadIdx.x;
-    if (i >= m) return;
+// a block per column: its nb partial sums in a fixed tree
+__global__ void __launch_bounds__(kA) k_rq_final(const double* __restrict__ part_num,
+                                                 const double* __restrict__ part_den, int nb,
+                                                 double* __restrict__ R,
+                                                 double* __restrict__ den_out) {
+    __shared__ double sh[2][kA / kWave];
+    const int i = blockIdx.x;
     double num = 0.0, den = 0.0;
-    for (int b = 0; b < nb; ++b) {
+    for (int b = threadIdx.x; b < nb; b += kA) {
         num += part_num[(int64_t)i * nb + b];
         den += part_den[(int64_t)i * nb + b];
+    }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        num += __shfl_xor(num, off, kWave);
+        den += __shfl_xor(den, off, kWave);
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        sh[0][threadIdx.x / kWave] = num;
+        sh[1][threadIdx.x / kWave] = den;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < kA / kWave; ++k) {
+        num += sh[0][k];
+        den += sh[1][k];
     }
     R[i] = den != 0.0 ? num / den : 0.0;
     if (den_out) den_out[i] = den;
 }
 
 // gw_e = sum_i gR_i [ (u_pi - u_qi)^2 - (B = D: R_i (u_pi^2 + u_qi^2)) ] / den_i
-__global__ void k_rq_backward(int64_t E, const int32_t* __restrict__ eu,
-                              const int32_t* __restrict__ ev, const double* __restrict__ U,
-                              int32_t m, int mode, const double* __restrict__ R,
-                              const double* __restrict__ den, const double* __restrict__ gR,
-                              double* __restrict__ gw) {
-    int64_t e = (int64_t)blockIdx.x * kA + threadIdx.x;
-    if (e >= E) return;
-    const double* up = U + (int64_t)eu[e] * m;
-    const double* uq = U + (int64_t)ev[e] * m;
-    double g = 0.0;
-    for (int i = 0; i < m; ++i) {
-        if (den[i] == 0.0) continue;
-        double df = up[i] - uq[i];
-        double t = df * df;
-        if (mode == GR_RQ_DEGREE) t -= R[i] * (up[i] * up[i] + uq[i] * uq[i]);
-        g = fma(gR[i] / den[i], t, g);
+template <int C>
+__global__ void __launch_bounds__(kRqThreads) k_rq_backward(
+    int64_t E, const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
+    const double* __restrict__ U, int32_t m, int cw, int mode, const double* __restrict__ R,
+    const double* __restrict__ den, const double* __restrict__ gR, double* __restrict__ gw) {
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int slots = kWave / cw, slot = lane / cw, cl = lane - slot * cw;
+    const int64_t b = ((int64_t)blockIdx.x * kRqWaves + wid) * slots * kRqU + slot;
+    double f[C], r[C];
+    bool use[C];
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        const double d = den[cl * C + k];
+        use[k] = d != 0.0;
+        f[k] = use[k] ? gR[cl * C + k] / d : 0.0;
+        r[k] = R[cl * C + k];
     }
-    gw[e] = g;
+    int32_t p[kRqU], q[kRqU];
+    double xp[kRqU][C], xq[kRqU][C];
+#pragma unroll
+    for (int u = 0; u < kRqU; ++u) {
+        const int64_t e = min(b + u * slots, E - 1);
+        p[u] = eu[e];
+        q[u] = ev[e];
+    }
+#pragma unroll
+    for (int u = 0; u < kRqU; ++u) {
+        rq_row<C>(U, p[u], m, cl, xp[u]);
+        rq_row<C>(U, q[u], m, cl, xq[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kRqU; ++u) {
+        double g = 0.0;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const double df = xp[u][k] - xq[u][k];
+            double t = df * df;
+            if (mode == GR_RQ_DEGREE) t -= r[k] * (xp[u][k] * xp[u][k] + xq[u][k] * xq[u][k]);
+            if (use[k]) g = fma(f[k], t, g);
+        }
+        // the edge's lanes, in order (every lane of the wave takes part)
+        double s = g;
+        for (int l = 1; l < cw; ++l) s += __shfl(g, min(lane + l, kWave - 1), kWave);
+        if (slot < slots && cl == 0 && b + u * slots < E) gw[b + u * slots] = s;
+    }
+}
+
+// whether a lane may take two columns per load
+static bool rq_pairs(const double* U, int32_t m) {
+    return m % 2 == 0 && (reinterpret_cast<uintptr_t>(U) & 15) == 0;
 }
 
 int rq_forward(int64_t n, int64_t E, const int32_t* eu, const int32_t* ev, const double* w,
@@ -228,18 +329,23 @@ int rq_forward(int64_t n, int64_t E, const int32_t* eu, const int32_t* ev, const
     size_t mark = ws.used;
     double* pn = ws.take<double>((size_t)kRqBlocks * m);
     double* pd = ws.take<double>((size_t)kRqBlocks * m);
-    double* pd2 = ws.take<double>((size_t)kRqBlocks * m);
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (rq)");
-    hipLaunchKernelGGL(k_rq_edges, dim3(kRqBlocks, m), dim3(kA), 0, st, E, eu, ev, w, U, m, mode, pn,
-                       pd);
-    GR_LAUNCHED("rq edges");
-    if (mode == GR_RQ_IDENTITY) {
-        hipLaunchKernelGGL(k_rq_nodes, dim3(kRqBlocks, m), dim3(kA), 0, st, n, U, m, pd2);
-        GR_LAUNCHED("rq nodes");
-        pd = pd2;
-    }
-    hipLaunchKernelGGL(k_rq_final, dim3(1), dim3(64), 0, st, (const double*)pn, (const double*)pd,
-                       kRqBlocks, m, R, den);
+    // no more blocks than the edges and nodes fill
+    const bool pair = rq_pairs(U, m);
+    const int cw = pair ? m / 2 : m;
+    const int64_t per = (int64_t)kRqWaves * (kWave / cw);
+    const int nb = (int)std::min<int64_t>(
+        kRqBlocks, std::max<int64_t>(1, std::max((E + per * kRqU - 1) / (per * kRqU),
+                                                 mode == GR_RQ_IDENTITY ? (n + per - 1) / per : 0)));
+    if (pair)
+        hipLaunchKernelGGL(k_rq_sums<2>, dim3(nb), dim3(kRqThreads), 0, st, n, E, eu, ev, w, U, m, cw,
+                           mode, pn, pd);
+    else
+        hipLaunchKernelGGL(k_rq_sums<1>, dim3(nb), dim3(kRqThreads), 0, st, n, E, eu, ev, w, U, m, cw,
+                           mode, pn, pd);
+    GR_LAUNCHED("rq sums");
+    hipLaunchKernelGGL(k_rq_final, dim3(m), dim3(kA), 0, st, (const double*)pn, (const double*)pd, nb,
+                       R, den);
     GR_LAUNCHED("rq final");
     ws.used = mark;
     return GR_OK;
@@ -301,8 +407,15 @@ int rq_backward(int64_t E, const int32_t* eu, const int32_t* ev, const double* U
                 int32_t mode, const double* R, const double* den, const double* gR, double* gw,
                 hipStream_t st) {
     if (E == 0) return GR_OK;
-    hipLaunchKernelGGL(k_rq_backward, dim3(blocks_for(E, kA)), dim3(kA), 0, st, E, eu, ev, U, m, mode,
-                       R, den, gR, gw);
+    const bool pair = rq_pairs(U, m);
+    const int cw = pair ? m / 2 : m;
+    const unsigned nb = blocks_for(E, kRqWaves * (kWave / cw) * kRqU);
+    if (pair)
+        hipLaunchKernelGGL(k_rq_backward<2>, dim3(nb), dim3(kRqThreads), 0, st, E, eu, ev, U, m, cw,
+                           mode, R, den, gR, gw);
+    else
+        hipLaunchKernelGGL(k_rq_backward<1>, dim3(nb), dim3(kRqThreads), 0, st, E, eu, ev, U, m, cw,
+                           mode, R, den, gR, gw);
     GR_LAUNCHED("rq backward");
     return GR_OK;
 }
