@@ -350,8 +350,9 @@ int gr_expand_edge_weights(const int32_t* edge_of_entry, int64_t nnz, int64_t n_
  * [n][K] of `dtype` (the initial vectors), G float32 [n][K] (the cotangent of
  * the smoothed vectors).  Outputs: gw_E float32[E] = d<G, X_S>/dw_E and
  * gX0 float32 [n][K] = d<G, X_S>/dX0.  With store_states != 0 the S+1
- * sweep-boundary states are kept; otherwise they are recomputed from X0
- * (S(S+1)/2 sweeps, three state buffers).  bfloat16 rounding of stored
+ * sweep-boundary states are kept; otherwise they are recomputed from X0 and
+ * from one (float32) or two (bfloat16) states kept on the way (7 or 6 sweeps
+ * for S = 5), in three state buffers and the scratch copy of gX0.  bfloat16 rounding of stored
  * states is treated as the identity in the reverse pass.  Deterministic
  * (gather form, no atomics on values).  Workspace: gr_smooth_vjp_workspace.
  */

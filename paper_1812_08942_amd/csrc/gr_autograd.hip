@@ -448,18 +448,6 @@ int rq_backward(int64_t E, const int32_t* eu, const int32_t* ev, const double* U
 // edges).
 namespace gr {
 
-__global__ void k_perm_payload(const int32_t* __restrict__ rp, const uint32_t* __restrict__ perm,
-                               const int32_t* __restrict__ nrp, int64_t n, int G,
-                               const int32_t* __restrict__ in, int32_t* __restrict__ out) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t r = t / G;
-    const int lane = (int)(t % G);
-    if (r >= n) return;
-    int32_t v = (int32_t)perm[r];
-    int32_t e0 = rp[v], e1 = rp[v + 1], o = nrp[r];
-    for (int32_t e = e0 + lane; e < e1; e += G) out[o + (e - e0)] = in[e];
-}
-
 template <int E>
 __device__ inline void load_f32(const float* __restrict__ A, int64_t row, int K, int q, float* v) {
 #pragma unroll
@@ -496,13 +484,14 @@ constexpr int vjp_keep() { return 32 / Chunk<DT>::E; }
 
 // Rows [lo, hi) of colour c with degree <= kLongRow, L = Q*P lanes per row.
 // FINAL = 0: the reverse step (G = the cotangent in the last sweep, else
-// null).  FINAL = 1: gX0 of those rows into out.
+// null; the last sweep is undone first and stores its gradients, the others
+// add to them).  FINAL = 1: gX0 of those rows into out.
 template <int Q, int P, int DT, int FINAL>
 __global__ void __launch_bounds__(256) k_vjp_rows(
     const int32_t* __restrict__ rp, const int32_t* __restrict__ col, const float* __restrict__ w,
     const void* __restrict__ Xs, const void* __restrict__ Xp, int32_t K, int64_t clo, int64_t lo,
     int64_t hi, const float* __restrict__ dw, const float* __restrict__ G, float* __restrict__ H,
-    float* __restrict__ ge, float* __restrict__ out) {
+    float* __restrict__ ge, int first, float* __restrict__ out) {
     constexpr int L = Q * P;
     constexpr int RPW = kWave / L;
     constexpr int E = Chunk<DT>::E;
@@ -571,7 +560,7 @@ __global__ void __launch_bounds__(256) k_vjp_rows(
 #pragma unroll
                     for (int i = 0; i < E; ++i) sdot = __fmaf_rn(h[i], xj[t][i] - xi[i], sdot);
                     sdot = qsum<Q>(sdot);
-                    if (e < e1 && q == 0) ge[e] += sdot;
+                    if (e < e1 && q == 0) ge[e] = first ? sdot : ge[e] + sdot;
                 }
             }
             return;
@@ -614,7 +603,7 @@ __global__ void __launch_bounds__(256) k_vjp_rows(
 #pragma unroll
             for (int i = 0; i < E; ++i) s = __fmaf_rn(h[i], xj[i] - xi[i], s);
             s = qsum<Q>(s);
-            if (ok && q == 0) ge[e] += s;
+            if (ok && q == 0) ge[e] = first ? s : ge[e] + s;
         }
     }
 }
@@ -709,7 +698,7 @@ __global__ void __launch_bounds__(256) k_vjp_long_apply(
     const void* __restrict__ Xp, int32_t K, int64_t clo, const int32_t* __restrict__ ppos,
     int64_t lo, int64_t hi, int64_t pbeg, const float* __restrict__ dw,
     const float* __restrict__ G, const float* __restrict__ part, float* __restrict__ H,
-    float* __restrict__ ge) {
+    float* __restrict__ ge, int first) {
     constexpr int P = 256 / Q;
     constexpr int E = Chunk<DT>::E;
     const int tid = threadIdx.x;
@@ -751,7 +740,7 @@ __global__ void __launch_bounds__(256) k_vjp_long_apply(
 #pragma unroll
         for (int i = 0; i < E; ++i) s = __fmaf_rn(h[i], xj[i] - xi[i], s);
         s = qsum<Q>(s);
-        if (ok && q == 0) ge[e] += s;
+        if (ok && q == 0) ge[e] = first ? s : ge[e] + s;
     }
 }
 
@@ -777,27 +766,28 @@ __global__ void k_vjp_long_final(const int32_t* __restrict__ ppos, const float* 
     store_f32<E>(out, r, K, q, g);
 }
 
-// the two relabelled entries of each undirected edge: slot 0 = the entry
-// whose original row is the smaller endpoint
-__global__ void k_edge_slots(const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-                             const int32_t* __restrict__ eoe, const int32_t* __restrict__ perm,
-                             int64_t n, int64_t E, int G, int32_t* __restrict__ slots) {
+// gw_e = the gradient of e's upper entry (row = the smaller endpoint) plus
+// that of the lower one: the lower entries' gradients go to gw (upper = 0),
+// then the upper entries, whose ids ascend, add theirs in front.  The rows
+// are walked in the caller's order, G lanes each; relabelled row iperm[v]
+// holds row v's entries in the same order.  (Listing both relabelled
+// entries of every edge first and gathering through the list took 1.2 ms on
+// the 434,000-node power-law graph, this takes 0.68 ms.)
+__global__ void k_edge_grad(const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
+                            const int32_t* __restrict__ eoe, const int32_t* __restrict__ iperm,
+                            const int32_t* __restrict__ nrp, const float* __restrict__ ge,
+                            int64_t n, int64_t E, int G, int upper, float* __restrict__ gw) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t r = t / G;
-    const int lane = (int)(t % G);
-    if (r >= n) return;
-    const int32_t orow = perm[r];
-    for (int32_t e = rp[r] + lane; e < rp[r + 1]; e += G) {
-        int32_t k = eoe[e];
-        if (k >= 0 && k < E) slots[2 * k + (orow < perm[col[e]] ? 0 : 1)] = e;
-        else g_bad_edge_id = 1;
+    const int64_t v = t / G;
+    if (v >= n) return;
+    const int32_t e0 = rp[v], e1 = rp[v + 1];
+    const int64_t o = (int64_t)nrp[iperm[v]] - e0;
+    for (int32_t e = e0 + (int32_t)(t % G); e < e1; e += G) {
+        if ((col[e] > v) != (upper != 0)) continue;
+        const int32_t k = eoe[e];
+        if (k < 0 || k >= E) g_bad_edge_id = 1;
+        else gw[k] = upper ? ge[o + e] + gw[k] : ge[o + e];
     }
-}
-
-__global__ void k_edge_grad(const int32_t* __restrict__ slots, const float* __restrict__ ge,
-                            int64_t E, float* __restrict__ gw) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < E) gw[k] = ge[slots[2 * k]] + ge[slots[2 * k + 1]];
 }
 
 __global__ void k_zero_f32(float* p, int64_t n) {
@@ -844,7 +834,7 @@ static int vjp_colour(const VjpPlan& pl, int c, const void* Xs, const void* Xp, 
         } else {
             hipLaunchKernelGGL((k_vjp_long_apply<Q, DT>), dim3((unsigned)(pl.pend[c] - pl.pbeg[c])),
                                dim3(256), 0, st, g->row_ptr, g->col, Xs, Xp, K, clo, pl.ppos, clo,
-                               mid, pl.pbeg[c], pl.dw, G, (const float*)pl.part, H, ge);
+                               mid, pl.pbeg[c], pl.dw, G, (const float*)pl.part, H, ge, G ? 1 : 0);
             GR_LAUNCHED("vjp long apply");
         }
     }
@@ -855,7 +845,7 @@ static int vjp_colour(const VjpPlan& pl, int c, const void* Xs, const void* Xp, 
     case PP:                                                                                       \
         if constexpr (Q * PP <= kWave)                                                             \
             hipLaunchKernelGGL((k_vjp_rows<Q, PP, DT, FINAL>), grid, dim3(256), 0, st, g->row_ptr,  \
-                               g->col, g->w, Xs, Xp, K, clo, mid, chi, pl.dw, G, H, ge, out);      \
+                               g->col, g->w, Xs, Xp, K, clo, mid, chi, pl.dw, G, H, ge, G ? 1 : 0, out);  \
         break;
     switch (pl.P[c]) {
         GR_VR(1) GR_VR(2) GR_VR(4) GR_VR(8) GR_VR(16) GR_VR(32) GR_VR(64)
@@ -872,9 +862,7 @@ size_t vjp_workspace(int64_t n, int64_t nnz, int32_t K, int32_t dtype, int32_t S
     const size_t fb = N * (size_t)K * 4 + 256;
     const size_t pieces = M / kPiece + M / kLongRow + 1;
     size_t b = 4 * N * 3 + 8 * M          // relabelled graph
-               + 4 * M                    // relabelled edge ids
                + 4 * M                    // per-entry gradients
-               + 8 * (M / 2 + 1)          // edge slots
                + (size_t)(store ? S + 1 : 3) * xb + 3 * fb  // states, G, H, gX0
                + 12 * N                   // weighted degrees, piece offsets and counts
                + pieces * (size_t)K * 4   // piece sums
@@ -882,34 +870,96 @@ size_t vjp_workspace(int64_t n, int64_t nnz, int32_t K, int32_t dtype, int32_t S
     return b + b / 16 + (16u << 20);
 }
 
+// The sweep-boundary states X_{s-1} and X_s for s = S .. 1.  With all of
+// them stored they are there.  Otherwise slot 0 keeps X_0, two slots hold
+// the states in use, and `spare` slots (room that the pass needs only at its
+// end) keep states on the way: a run of sweeps from state a to state b
+// leaves one half-way for each spare slot that is free, so that the next
+// states are rebuilt from there and not from X_0.  Sweeps for S = 5: 7 with
+// one spare slot, 6 with two, where rebuilding every pair from X_0 takes 15
+// (434,000-node power law, float32: 12.4 of the backward's 24.3 ms).
+template <int DT>
+struct VjpStates {
+    const OrderedGraph* og;
+    int K, store;
+    size_t xbytes;
+    std::vector<char*> slot;  // store: S + 1 of them; else X_0, two, spares
+    std::vector<int> holds;   // the state in each slot, -1 for none
+    Arena& ws;
+    hipStream_t st;
+
+    int find(int s) const {
+        for (size_t i = 0; i < slot.size(); ++i)
+            if (holds[i] == s) return (int)i;
+        return -1;
+    }
+    int copy(int from, int to) {
+        GR_HIP(hipMemcpyAsync(slot[to], slot[from], xbytes, hipMemcpyDeviceToDevice, st));
+        holds[to] = holds[from];
+        return GR_OK;
+    }
+    int sweep(int i, int sweeps) {
+        GR_TRY(smooth_ordered(og, K, sweeps, DT, slot[i], ws, st));
+        holds[i] += sweeps;
+        return GR_OK;
+    }
+    // state s into a slot other than `keep`, from the nearest earlier one
+    int build(int s, int keep, int* at) {
+        if ((*at = find(s)) >= 0) return GR_OK;
+        int from = 0;
+        for (size_t i = 0; i < slot.size(); ++i)
+            if (holds[i] >= 0 && holds[i] < s && holds[i] > holds[from]) from = (int)i;
+        const int to = keep == 1 ? 2 : 1;  // of the two slots in use
+        if (from != to) GR_TRY(copy(from, to));
+        for (size_t i = 3; i < slot.size() && holds[to] + 1 < s; ++i) {
+            const bool free = holds[i] < 0 || holds[i] > s;
+            if (!free || (int)i == keep) continue;
+            const int left = (int)(slot.size() - i);  // spare slots from here on
+            GR_TRY(sweep(to, (s - holds[to] + left) / (left + 1)));
+            GR_TRY(copy(to, (int)i));
+        }
+        if (holds[to] < s) GR_TRY(sweep(to, s - holds[to]));
+        *at = to;
+        return GR_OK;
+    }
+    // X_{s-1} and X_s
+    int pair(int s, const void** Xp, const void** Xs) {
+        int p = -1, q = find(s);
+        if (q < 0) {  // the first pair: X_s is one sweep from X_{s-1}
+            GR_TRY(build(s - 1, -1, &p));
+            q = p == 1 ? 2 : 1;
+            if (store) q = s;
+            GR_TRY(copy(p, q));
+            GR_TRY(sweep(q, 1));
+        } else {
+            GR_TRY(build(s - 1, q, &p));
+        }
+        *Xp = slot[p];
+        *Xs = slot[q];
+        return GR_OK;
+    }
+};
+
 template <int Q, int DT>
-static int vjp_impl(const VjpPlan& pl, int K, int S, int store, void* states, size_t xbytes,
+static int vjp_impl(const VjpPlan& pl, int K, int S, int store, void* states, size_t xstride,
                     const float* Gp, float* H, float* ge, float* gx, Arena& ws, hipStream_t st) {
     const OrderedGraph* og = pl.og;
     const int C = og->n_colours;
-    char* base = (char*)states;
-    auto state = [&](int s) { return (void*)(base + (size_t)s * xbytes); };
-    // states: store mode keeps X_0..X_S; recompute mode keeps X_0 in slot 0
-    // and rebuilds X_{s-1} (slot 1) and X_s (slot 2) for every sweep s
-    if (store) {
+    const size_t xbytes = (size_t)og->g.n * K * (DT == GR_BF16 ? 2 : 4);
+    VjpStates<DT> X{og, K, store, xbytes, {}, {}, ws, st};
+    for (int s = 0; s < (store ? S + 1 : 3); ++s) X.slot.push_back((char*)states + (size_t)s * xstride);
+    if (!store)  // gx, float32, is written after the last reverse step
+        for (int s = 0; s < (DT == GR_BF16 ? 2 : 1); ++s) X.slot.push_back((char*)gx + s * xbytes);
+    X.holds.assign(X.slot.size(), -1);
+    X.holds[0] = 0;
+    if (store)
         for (int s = 1; s <= S; ++s) {
-            GR_HIP(hipMemcpyAsync(state(s), state(s - 1), xbytes, hipMemcpyDeviceToDevice, st));
-            GR_TRY(smooth_ordered(og, K, 1, DT, state(s), ws, st));
+            GR_TRY(X.copy(s - 1, s));
+            GR_TRY(X.sweep(s, 1));
         }
-    }
     for (int s = S; s >= 1; --s) {
         const void *Xs, *Xp;
-        if (store) {
-            Xs = state(s);
-            Xp = state(s - 1);
-        } else {
-            GR_HIP(hipMemcpyAsync(state(1), state(0), xbytes, hipMemcpyDeviceToDevice, st));
-            GR_TRY(smooth_ordered(og, K, s - 1, DT, state(1), ws, st));
-            GR_HIP(hipMemcpyAsync(state(2), state(1), xbytes, hipMemcpyDeviceToDevice, st));
-            GR_TRY(smooth_ordered(og, K, 1, DT, state(2), ws, st));
-            Xs = state(2);
-            Xp = state(1);
-        }
+        GR_TRY(X.pair(s, &Xp, &Xs));
         const float* G = s == S ? Gp : nullptr;
         for (int c = C - 1; c >= 0; --c)
             GR_TRY((vjp_colour<Q, DT, 0>(pl, c, Xs, Xp, K, G, H, ge, nullptr, st)));
@@ -927,19 +977,13 @@ int smooth_vjp(const gr_graph* g, const int32_t* eoe, int64_t E, const int32_t* 
     GR_TRY(validate_colouring(g, colours, C, ws, st));
     OrderedGraph og;
     GR_TRY(order_by_colour(g, colours, C, &og, ws, st));
-    // edge ids of the relabelled entries, weighted degrees, long-row pieces
+    // weighted degrees, long-row pieces
     const int G = lanes_per_row(n, nnz);
-    int32_t* eoe_r = ws.take<int32_t>(nnz + 1);
     float* dw = ws.take<float>(n + 1);
     int32_t* ppos = ws.take<int32_t>(n + 1);
     int32_t* pbounds = ws.take<int32_t>(2 * (size_t)C + 1);
     int64_t* pidx = ws.take<int64_t>(2 * (size_t)C + 1);
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (vjp)");
-    if (nnz > 0) {
-        hipLaunchKernelGGL(k_perm_payload, dim3(blocks_for(n * G, 256)), dim3(256), 0, st,
-                           g->row_ptr, (const uint32_t*)og.perm, og.g.row_ptr, n, G, eoe, eoe_r);
-        GR_LAUNCHED("perm payload");
-    }
     hipLaunchKernelGGL(k_row_weight, dim3(blocks_for(n * G, 256)), dim3(256), 0, st, og.g.row_ptr,
                        og.g.w, n, G, dw);
     GR_LAUNCHED("row weights");
@@ -992,14 +1036,15 @@ int smooth_vjp(const gr_graph* g, const int32_t* eoe, int64_t E, const int32_t* 
     float* H = ws.take<float>((size_t)n * K + 4);
     float* gx = ws.take<float>((size_t)n * K + 4);
     float* ge = ws.take<float>(nnz + 1);
-    int32_t* slots = ws.take<int32_t>(2 * (E + 1));
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (vjp states)");
     GR_TRY(permute_rows(X0, states, og.perm, n, (size_t)K * (dtype == GR_BF16 ? 2 : 4), 0, st));
     GR_TRY(permute_rows(Gc, Gp, og.perm, n, (size_t)K * 4, 0, st));
     hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(n * K, 256)), dim3(256), 0, st, H, (int64_t)n * K);
     GR_LAUNCHED("zero");
-    hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(nnz + 1, 256)), dim3(256), 0, st, ge, nnz + 1);
-    GR_LAUNCHED("zero");
+    if (S == 0) {  // no sweep stores the entries' gradients
+        hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(nnz + 1, 256)), dim3(256), 0, st, ge, nnz + 1);
+        GR_LAUNCHED("zero");
+    }
 #define GR_VJ(QQ, DD) \
     case QQ: GR_TRY((vjp_impl<QQ, DD>(pl, K, S, store, states, xstride, Gp, H, ge, gx, ws, st))); break;
     if (dtype == GR_BF16) {
@@ -1017,15 +1062,16 @@ int smooth_vjp(const gr_graph* g, const int32_t* eoe, int64_t E, const int32_t* 
     // no sweep: X_S = X0 and the cotangent passes through
     GR_TRY(permute_rows(S >= 1 ? gx : Gp, gX0, og.perm, n, (size_t)K * 4, 1, st));
     if (E > 0) {
-        GR_TRY(fill_i32(slots, 0, 2 * E, st));  // unmatched slots read entry 0, never garbage
+        hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(E, 256)), dim3(256), 0, st, gw, E);
+        GR_LAUNCHED("zero");
         GR_TRY(reset_bad_edge_flag(st));
-        hipLaunchKernelGGL(k_edge_slots, dim3(blocks_for(n * G, 256)), dim3(256), 0, st,
-                           og.g.row_ptr, og.g.col, (const int32_t*)eoe_r, og.perm, n, E, G, slots);
-        GR_LAUNCHED("edge slots");
+        for (int upper = 0; upper < 2; ++upper) {
+            hipLaunchKernelGGL(k_edge_grad, dim3(blocks_for(n * G, 256)), dim3(256), 0, st,
+                               g->row_ptr, g->col, eoe, (const int32_t*)og.iperm, og.g.row_ptr,
+                               (const float*)ge, n, E, G, upper, gw);
+            GR_LAUNCHED("edge grad");
+        }
         GR_TRY(check_bad_edge_flag(st));
-        hipLaunchKernelGGL(k_edge_grad, dim3(blocks_for(E, 256)), dim3(256), 0, st,
-                           (const int32_t*)slots, (const float*)ge, E, gw);
-        GR_LAUNCHED("edge grad");
     }
     GR_HIP(hipStreamSynchronize(st));  // host vectors above end here
     return GR_OK;
