@@ -837,11 +837,11 @@ __global__ void k_place_lower(const uint32_t* __restrict__ mkey, const uint32_t*
 }
 
 // the stable radix sort for either key width
-static int sort_pairs(uint32_t* a, uint32_t* av, uint32_t* b, uint32_t* bv, int64_t n, int bits,
+static int sort_pairs(uint32_t*& a, uint32_t*& av, uint32_t*& b, uint32_t*& bv, int64_t n, int bits,
                       Arena& ws, hipStream_t st) {
     return radix_sort_pairs32(a, av, b, bv, n, bits, ws, st);
 }
-static int sort_pairs(uint64_t* a, uint32_t* av, uint64_t* b, uint32_t* bv, int64_t n, int bits,
+static int sort_pairs(uint64_t*& a, uint32_t*& av, uint64_t*& b, uint32_t*& bv, int64_t n, int bits,
                       Arena& ws, hipStream_t st) {
     return radix_sort_pairs(a, av, b, bv, n, bits, ws, st);
 }

@@ -44,7 +44,7 @@ static size_t plan_bytes(int64_t n, int64_t nnz, int32_t K, int32_t dtype) {
     const size_t N = (size_t)n + 1, M = (size_t)nnz + 1;
     auto sort_scratch = [](size_t m) { return 2 * 256 * 4 * (m / 2048 + 1) + m / 64 + 256 * 1024; };
     size_t persistent = 4 * N                                  // colours
-                        + 4 * N * 3 + 8 * M                    // relabelled graph
+                        + 4 * N * 4 + 8 * M                    // relabelled graph
                         + vec_bytes(n, K, dtype) + 256         // X
                         + 4 * N * 4                            // best, abest, agg (two)
                         + 2 * (4 * N + 8 * M)                  // coarse ping-pong

@@ -861,7 +861,7 @@ size_t vjp_workspace(int64_t n, int64_t nnz, int32_t K, int32_t dtype, int32_t S
     const size_t xb = N * (size_t)K * (dtype == GR_BF16 ? 2 : 4) + 256;
     const size_t fb = N * (size_t)K * 4 + 256;
     const size_t pieces = M / kPiece + M / kLongRow + 1;
-    size_t b = 4 * N * 3 + 8 * M          // relabelled graph
+    size_t b = 4 * N * 4 + 8 * M          // relabelled graph
                + 4 * M                    // per-entry gradients
                + (size_t)(store ? S + 1 : 3) * xb + 3 * fb  // states, G, H, gX0
                + 12 * N                   // weighted degrees, piece offsets and counts

@@ -660,13 +660,16 @@ static int colour_flow(const gr_graph* g, uint64_t seed, int ldf, int32_t* colou
     // not, the bounded waits would end the call with GR_EHIP, never hang).
     // It exists for profiling: rocprofv3 faults in its own exit handlers
     // after a cooperative launch, once its results are written.
-    // width of the priority sort key (32; the variable GR_COLOUR_KEY_BITS=b,
-    // 8 <= b <= 32, keeps fewer bits of h, which makes ties of the truncated
-    // keys frequent, for tests of their exact order)
-    int hbits = 32;
+    // width of the priority sort key: five bits more than the nodes need, so
+    // that few share a key, in whole passes (24 bits up to 524,288 nodes: a
+    // pass less than 32).  The largest-degree-first key always takes 32.
+    // The variable GR_COLOUR_KEY_BITS=b, 8 <= b <= 32, sets the bits of h,
+    // which makes ties of the truncated keys frequent, for tests of their
+    // exact order.
+    int key_bits = 32, hbits = std::min(32, (bits_for(n) + 5 + 7) / 8 * 8);
     if (const char* kb_env = getenv("GR_COLOUR_KEY_BITS")) {
         const int b = atoi(kb_env);
-        if (b >= 8 && b <= 32) hbits = b;
+        if (b >= 8 && b <= 32) hbits = key_bits = b;
     }
     const char* plain_env = getenv("GR_COLOUR_PLAIN_LAUNCH");
     const bool plain = plain_env && plain_env[0] == '1';
@@ -681,7 +684,7 @@ static int colour_flow(const gr_graph* g, uint64_t seed, int ldf, int32_t* colou
         uint32_t* ka32 = reinterpret_cast<uint32_t*>(ka);
         uint32_t* kb32 = reinterpret_cast<uint32_t*>(kb);
         hipLaunchKernelGGL(k_prio_keys, dim3(nb), dim3(kThreads), 0, st, g->row_ptr, n, seed, mode,
-                           hbits, (const int32_t*)small, ka32, va);
+                           mode ? key_bits : hbits, (const int32_t*)small, ka32, va);
         GR_LAUNCHED("colour keys");
         GR_TRY(radix_sort_pairs32(ka32, va, kb32, order, n, mode ? 32 : hbits, ws, st));
         hipLaunchKernelGGL(k_order_ties, dim3(nb), dim3(kThreads), 0, st, (const uint32_t*)kb32, order,
@@ -893,7 +896,9 @@ int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours
                     Arena& ws, hipStream_t st) {
     const int64_t n = g->n, nnz = g->nnz;
     og->n_colours = n_colours;
-    og->perm = ws.take<int32_t>(n);
+    // the sort's two value buffers: the permutation ends in either
+    uint32_t* perm = ws.take<uint32_t>(n);
+    uint32_t* v0 = ws.take<uint32_t>(n);
     og->iperm = ws.take<int32_t>(n);
     int32_t* nrp = ws.take<int32_t>(n + 1);
     int32_t* ncol = ws.take<int32_t>(nnz);
@@ -902,7 +907,6 @@ int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours
     size_t mark = ws.used;
     const int32_t nb = kNT * n_colours;
     uint32_t* k0 = ws.take<uint32_t>(n);
-    uint32_t* v0 = ws.take<uint32_t>(n);
     uint32_t* k1 = ws.take<uint32_t>(n);
     int32_t* bfirst = ws.take<int32_t>(nb + 1);
     int32_t* bend = ws.take<int32_t>(nb + 1);
@@ -916,7 +920,8 @@ int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours
                            g->row_ptr, colours, n, k0, v0);
         GR_LAUNCHED("bucket keys");
     }
-    GR_TRY(radix_sort_pairs32(k0, v0, k1, (uint32_t*)og->perm, n, bits_for(nb), ws, st));
+    GR_TRY(radix_sort_pairs32(k0, v0, k1, perm, n, bits_for(nb), ws, st));
+    og->perm = reinterpret_cast<int32_t*>(perm);
     if (n > 0) {
         hipLaunchKernelGGL(k_bucket_bounds, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st,
                            (const uint32_t*)k1, n, bfirst, bend);

@@ -3,6 +3,8 @@
 // atomics; every reduction order is fixed by the problem size alone.
 #include "gr_internal.hpp"
 
+#include <algorithm>
+
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -181,10 +183,13 @@ __global__ void __launch_bounds__(kScanThreads) k_tile_sums(const T* __restrict_
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
+// Scan of each tile after the tiles before it: part_off holds the offsets,
+// or, with sums, the tiles' sums, which every block adds up for itself (a
+// launch less; the reads stay in L2).
 template <class T>
 __global__ void __launch_bounds__(kScanThreads) k_tile_scan(const T* __restrict__ in, T* __restrict__ out,
                                                             int64_t n, const T* __restrict__ part_off,
-                                                            T* __restrict__ total, int vec) {
+                                                            T* __restrict__ total, int vec, int sums) {
     constexpr int V = 16 / sizeof(T);
     int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     T vals[kScanItems];
@@ -192,8 +197,15 @@ __global__ void __launch_bounds__(kScanThreads) k_tile_scan(const T* __restrict_
     T s = 0;
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) s += vals[i];
-    T tot;
-    T run = block_exclusive_scan(s, &tot) + (part_off ? part_off[blockIdx.x] : T(0));
+    T tot, off = 0;
+    if (sums) {
+        T before = 0;
+        for (unsigned i = threadIdx.x; i < blockIdx.x; i += kScanThreads) before += part_off[i];
+        block_exclusive_scan(before, &off);
+    } else if (part_off) {
+        off = part_off[blockIdx.x];
+    }
+    T run = block_exclusive_scan(s, &tot) + off;
     if (vec && base + kScanItems <= n) {
 #pragma unroll
         for (int i = 0; i < kScanItems; i += V) {
@@ -216,6 +228,54 @@ __global__ void __launch_bounds__(kScanThreads) k_tile_scan(const T* __restrict_
     if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) *total = run;
 }
 
+// One workgroup of kOneThreads threads scans up to kOneScan values, kScanItems
+// consecutive ones per thread: small arrays, and the digit counts of sorts
+// of up to 131,072 keys, take one launch instead of three.
+constexpr int kOneThreads = 1024;
+constexpr int64_t kOneScan = (int64_t)kOneThreads * kScanItems;
+
+template <class T>
+__global__ void __launch_bounds__(kOneThreads) k_one_scan(const T* __restrict__ in, T* __restrict__ out,
+                                                          int64_t n, T* __restrict__ total, int vec) {
+    constexpr int V = 16 / sizeof(T);
+    __shared__ T wsum[kOneThreads / kWave];
+    const int64_t base = (int64_t)threadIdx.x * kScanItems;
+    T vals[kScanItems];
+    scan_load<T>(in, base, n, vec != 0, vals);
+    T s = 0;
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) s += vals[i];
+    const T inc = wave_inclusive_scan(s);
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) wsum[threadIdx.x / kWave] = inc;
+    __syncthreads();
+    T run = inc - s;
+    for (unsigned w = 0; w < threadIdx.x / kWave; ++w) run += wsum[w];
+    if (vec && base + kScanItems <= n) {
+#pragma unroll
+        for (int i = 0; i < kScanItems; i += V) {
+            uint4 u;
+            T* t = reinterpret_cast<T*>(&u);
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                t[k] = run;
+                run += vals[i + k];
+            }
+            *reinterpret_cast<uint4*>(out + base + i) = u;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i) {
+            if (base + i < n) out[base + i] = run;
+            run += vals[i];
+        }
+    }
+    if (total && threadIdx.x == kOneThreads - 1) *total = run;
+}
+
+// tiles up to which every block of the second launch adds up the tiles
+// before it (4,096 tiles: 33 MB of reads in all)
+constexpr unsigned kSumTiles = 4096;
+
 template <class T>
 static int scan_exclusive(const T* in, T* out, int64_t n, T* total, Arena& ws, hipStream_t st) {
     if (n <= 0) {
@@ -224,10 +284,14 @@ static int scan_exclusive(const T* in, T* out, int64_t n, T* total, Arena& ws, h
     }
     unsigned nb = blocks_for(n, kScanTile);
     const int vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-    if (nb == 1) {
+    if (nb == 1 || n <= kOneScan) {
         if (ws.sizing()) return GR_OK;
-        hipLaunchKernelGGL(k_tile_scan<T>, dim3(1), dim3(kScanThreads), 0, st, in, out, n,
-                           (const T*)nullptr, total, vec);
+        if (nb == 1)
+            hipLaunchKernelGGL(k_tile_scan<T>, dim3(1), dim3(kScanThreads), 0, st, in, out, n,
+                               (const T*)nullptr, total, vec, 0);
+        else
+            hipLaunchKernelGGL(k_one_scan<T>, dim3(1), dim3(kOneThreads), 0, st, in, out, n, total,
+                               vec);
         GR_LAUNCHED("scan");
         return GR_OK;
     }
@@ -239,10 +303,11 @@ static int scan_exclusive(const T* in, T* out, int64_t n, T* total, Arena& ws, h
         hipLaunchKernelGGL(k_tile_sums<T>, dim3(nb), dim3(kScanThreads), 0, st, in, n, part, vec);
         GR_LAUNCHED("scan partials");
     }
-    GR_TRY(scan_exclusive<T>(part, part_off, nb, (T*)nullptr, ws, st));
+    const int sums = nb <= kSumTiles;
+    if (!sums) GR_TRY(scan_exclusive<T>(part, part_off, nb, (T*)nullptr, ws, st));
     if (!ws.sizing()) {
         hipLaunchKernelGGL(k_tile_scan<T>, dim3(nb), dim3(kScanThreads), 0, st, in, out, n,
-                           (const T*)part_off, total, vec);
+                           (const T*)(sums ? part : part_off), total, vec, sums);
         GR_LAUNCHED("scan");
     }
     if (!ws.sizing()) ws.used = mark;  // scratch released (stream order keeps it valid)
@@ -394,20 +459,133 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_scatter(
     }
 }
 
+// All passes of the sort in one workgroup, for up to kBlockSort keys: the
+// keys and values stay in registers (IT of each per thread, wave w owning
+// IT * 64 consecutive ones) and change places through LDS once per pass,
+// ranked as in the scatter above.  Launch by launch a pass of a few thousand
+// keys takes the three launches' 16 us, here 4 us.
+constexpr int kBlockSortThreads = 1024;
+constexpr int kBlockSortWaves = kBlockSortThreads / kWave;
+constexpr int64_t kBlockSort = 8 * kBlockSortThreads;
+
+template <class KT, int IT>
+__global__ void __launch_bounds__(kBlockSortThreads) k_block_sort(
+    const KT* __restrict__ kin, const uint32_t* __restrict__ vin, KT* __restrict__ kout,
+    uint32_t* __restrict__ vout, int n, int passes) {
+    __shared__ KT skey[IT * kBlockSortThreads];
+    __shared__ uint32_t sval[IT * kBlockSortThreads];
+    __shared__ int32_t wcnt[kBlockSortWaves][kRadix];  // per wave: its count, then its place
+    __shared__ int32_t wsum[kRadix / kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+    KT key[IT];
+    uint32_t val[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int i = (wid * IT + it) * kWave + lane;
+        key[it] = i < n ? kin[i] : KT(0);
+        val[it] = i < n ? vin[i] : 0u;
+    }
+    for (int p = 0; p < passes; ++p) {
+        const int shift = 8 * p;
+        for (int i = tid; i < kBlockSortWaves * kRadix; i += kBlockSortThreads)
+            wcnt[i / kRadix][i % kRadix] = 0;
+        __syncthreads();
+        uint64_t peer[IT];
+        int dig[IT];
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int i = (wid * IT + it) * kWave + lane;
+            const int d = i < n ? (int)((key[it] >> shift) & 0xff) : kRadix;
+            uint64_t peers = ~0ull;
+#pragma unroll
+            for (int b = 0; b < 9; ++b) {
+                const uint64_t bb = __ballot((d >> b) & 1);
+                peers &= ((d >> b) & 1) ? bb : ~bb;
+            }
+            dig[it] = d;
+            peer[it] = peers;
+            if (d < kRadix && (peers & lt) == 0) wcnt[wid][d] += __popcll(peers);
+        }
+        __syncthreads();
+        // digit tid: the keys of smaller digits, then each wave's place
+        int32_t c = 0, x = 0;
+        if (tid < kRadix) {
+            for (int w = 0; w < kBlockSortWaves; ++w) c += wcnt[w][tid];
+            x = c;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const int32_t y = __shfl_up(x, off, kWave);
+                if (lane >= off) x += y;
+            }
+            if (lane == kWave - 1) wsum[wid] = x;
+        }
+        __syncthreads();
+        if (tid < kRadix) {
+            int32_t place = x - c;
+            for (int w = 0; w < wid; ++w) place += wsum[w];
+            for (int w = 0; w < kBlockSortWaves; ++w) {
+                const int32_t cw = wcnt[w][tid];
+                wcnt[w][tid] = place;
+                place += cw;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int d = dig[it];
+            if (d < kRadix) {
+                const int at = wcnt[wid][d] + __popcll(peer[it] & lt);
+                skey[at] = key[it];
+                sval[at] = val[it];
+                // moved on by the digit's lowest lane, after every lane of the
+                // digit has read it (a wave's LDS accesses are in order)
+                if ((peer[it] & lt) == 0) wcnt[wid][d] += __popcll(peer[it]);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int i = (wid * IT + it) * kWave + lane;
+            if (i < n) {
+                key[it] = skey[i];
+                val[it] = sval[i];
+            }
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int i = (wid * IT + it) * kWave + lane;
+        if (i < n) {
+            kout[i] = key[it];
+            vout[i] = val[it];
+        }
+    }
+}
+
+// Results in keys_out / vals_out, which may have changed places with the
+// inputs (both are scratch otherwise).
 template <class KT>
-static int radix_sort(KT* keys_in, uint32_t* vals_in, KT* keys_out, uint32_t* vals_out, int64_t n,
+static int radix_sort(KT*& keys_in, uint32_t*& vals_in, KT*& keys_out, uint32_t*& vals_out, int64_t n,
                       int bits, Arena& ws, hipStream_t st) {
-    int passes = (bits + 7) / 8;
+    const int passes = (bits + 7) / 8;
+    if (n <= 0) return GR_OK;
+    if (n <= kBlockSort) {
+#define GR_BLOCK_SORT(IT)                                                                          \
+    hipLaunchKernelGGL((k_block_sort<KT, IT>), dim3(1), dim3(kBlockSortThreads), 0, st,            \
+                       (const KT*)keys_in, (const uint32_t*)vals_in, keys_out, vals_out, (int)n, passes)
+        if (n <= 2 * kBlockSortThreads) GR_BLOCK_SORT(2);
+        else if (n <= 4 * kBlockSortThreads) GR_BLOCK_SORT(4);
+        else GR_BLOCK_SORT(8);
+#undef GR_BLOCK_SORT
+        GR_LAUNCHED("block sort");
+        return GR_OK;
+    }
     unsigned nb = blocks_for(n, kSortTile);
     size_t mark = ws.used;
     int32_t* hist = ws.take<int32_t>((size_t)kRadix * nb);
     int32_t* offs = ws.take<int32_t>((size_t)kRadix * nb);
-    if (ws.sizing()) {
-        GR_TRY(scan_exclusive_i32(nullptr, nullptr, (int64_t)kRadix * nb, nullptr, ws, st));
-        return GR_OK;
-    }
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (sort)");
-    if (n <= 0) return GR_OK;
     KT* ks = keys_in;
     uint32_t* vs = vals_in;
     KT* kd = keys_out;
@@ -421,24 +599,24 @@ static int radix_sort(KT* keys_in, uint32_t* vals_in, KT* keys_out, uint32_t* va
         hipLaunchKernelGGL(k_radix_scatter<KT>, dim3(nb), dim3(kSortThreads), 0, st, ks, vs, kd, vd,
                            n, shift, (const int32_t*)offs, (int)nb);
         GR_LAUNCHED("radix scatter");
-        KT* tk = ks; ks = kd; kd = tk;
-        uint32_t* tv = vs; vs = vd; vd = tv;
+        std::swap(ks, kd);
+        std::swap(vs, vd);
     }
-    if (ks != keys_out) {
-        GR_HIP(hipMemcpyAsync(keys_out, ks, sizeof(KT) * n, hipMemcpyDeviceToDevice, st));
-        GR_HIP(hipMemcpyAsync(vals_out, vs, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, st));
-    }
+    keys_out = ks;
+    vals_out = vs;
+    keys_in = kd;
+    vals_in = vd;
     ws.used = mark;
     return GR_OK;
 }
 
-int radix_sort_pairs(uint64_t* keys_in, uint32_t* vals_in, uint64_t* keys_out, uint32_t* vals_out,
-                     int64_t n, int bits, Arena& ws, hipStream_t st) {
+int radix_sort_pairs(uint64_t*& keys_in, uint32_t*& vals_in, uint64_t*& keys_out,
+                     uint32_t*& vals_out, int64_t n, int bits, Arena& ws, hipStream_t st) {
     return radix_sort<uint64_t>(keys_in, vals_in, keys_out, vals_out, n, bits, ws, st);
 }
 
-int radix_sort_pairs32(uint32_t* keys_in, uint32_t* vals_in, uint32_t* keys_out,
-                       uint32_t* vals_out, int64_t n, int bits, Arena& ws, hipStream_t st) {
+int radix_sort_pairs32(uint32_t*& keys_in, uint32_t*& vals_in, uint32_t*& keys_out,
+                       uint32_t*& vals_out, int64_t n, int bits, Arena& ws, hipStream_t st) {
     if (bits > 32) return set_error(GR_EINVAL, "a 32-bit sort key has at most 32 bits");
     return radix_sort<uint32_t>(keys_in, vals_in, keys_out, vals_out, n, bits, ws, st);
 }
