@@ -19,7 +19,9 @@
  *   memory: scratch comes from the caller's workspace `ws` of `ws_bytes`
  *   bytes (size it with gr_workspace_size), except for the one fixed static
  *   array that gr_rq_forward_noalloc uses instead of a workspace.  Outputs
- *   have caller-allocated upper-bound sizes.
+ *   have caller-allocated upper-bound sizes.  Sizes and flags come back
+ *   through pinned host pages (64 KiB each, at most 16 per process, shared by
+ *   all threads, freed at exit).
  * Streams.  `stream` is a hipStream_t (NULL = the null stream).  Work is
  *   enqueued on it; an entry point returns only after the device-to-host
  *   size reads it documents, otherwise asynchronously.

@@ -319,8 +319,7 @@ int find_long_rows(const gr_graph* g, int32_t** rows, int64_t* n_long, Arena& ws
                        pos, n, out);
     GR_LAUNCHED("long scatter");
     int32_t cnt = 0;
-    GR_HIP(hipMemcpyAsync(&cnt, pos + n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{pos + n, sizeof(int32_t)}}, &cnt, st));
     *rows = out;
     *n_long = cnt;
     return GR_OK;

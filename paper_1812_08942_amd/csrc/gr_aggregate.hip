@@ -157,8 +157,7 @@ int aggregate(const gr_graph* g, const int32_t* best, const float* dbest, const 
     GR_LAUNCHED("forest own");
     GR_TRY(scan_exclusive_i32(own, pos, n, pos + n, ws, st));
     int32_t nf = 0;
-    GR_HIP(hipMemcpyAsync(&nf, pos + n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{pos + n, sizeof(int32_t)}}, &nf, st));
     if (n_forest) *n_forest = nf;
     const int32_t* accepted = acc;  // the forest edges taken
     if (n - nf >= target) {
@@ -166,7 +165,7 @@ int aggregate(const gr_graph* g, const int32_t* best, const float* dbest, const 
     } else {
         // accept only the first m = n - target forest edges in the total order
         int64_t m = n - target;
-        GR_HIP(hipMemsetAsync(acc, 0, sizeof(int32_t) * n, st));
+        GR_TRY(fill_i32(acc, 0, n, st));
         if (m > 0) {
             size_t mark2 = ws.used;
             uint64_t* k1 = ws.take<uint64_t>(nf);
@@ -200,36 +199,35 @@ int aggregate(const gr_graph* g, const int32_t* best, const float* dbest, const 
     // launch (a launch at least multiplies the distance covered by kHops).
     // Launches go in batches of kJumpBatch with one host check: only the
     // batch's last launch reports, and a launch that moves nothing means
-    // every later one moves nothing too
+    // every later one moves nothing too.  The ids are assigned as if the
+    // batch had been enough, as it usually is, and the check comes with
+    // their number.
     constexpr int kJumpBatch = 2;
+    int32_t* root = pa;
+    int32_t* minid = pb;
+    int32_t* flag_by_id = own;   // reuse
+    int32_t* rank_by_id = acc;   // reuse (no longer needed)
+    int32_t nc = 0;
     for (int round = 0;; round += kJumpBatch) {
         if (round > 32) return set_error(GR_EHIP, "pointer jumping did not converge");
-        GR_HIP(hipMemsetAsync(small, 0, sizeof(int32_t), st));
+        GR_TRY(fill_many({{small, 0, 2}, {minid, 0x7fffffff, n}}, st));
         for (int b = 0; b < kJumpBatch; ++b) {
             hipLaunchKernelGGL(k_jump, dim3(gb), dim3(kT), 0, st, pa, n,
                                b == kJumpBatch - 1 ? small : (int32_t*)nullptr);
             GR_LAUNCHED("jump");
         }
-        int32_t ch = 0;
-        GR_HIP(hipMemcpyAsync(&ch, small, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        GR_HIP(hipStreamSynchronize(st));
-        if (!ch) break;
+        hipLaunchKernelGGL(k_min_member, dim3(gb), dim3(kT), 0, st, root, ids, n, minid);
+        GR_LAUNCHED("min member");
+        hipLaunchKernelGGL(k_leader_flags, dim3(gb), dim3(kT), 0, st, root, ids, minid, n, flag_by_id);
+        GR_LAUNCHED("leader flags");
+        GR_TRY(scan_exclusive_i32(flag_by_id, rank_by_id, n, small + 1, ws, st));
+        hipLaunchKernelGGL(k_assign, dim3(gb), dim3(kT), 0, st, root, minid, rank_by_id, n, agg);
+        GR_LAUNCHED("assign");
+        int32_t hs[2] = {0, 0};  // whether the last launch moved a pointer, aggregates
+        GR_TRY(fetch({{small, sizeof(hs)}}, hs, st));
+        nc = hs[1];
+        if (!hs[0]) break;
     }
-    int32_t* root = pa;
-    int32_t* minid = pb;  // reuse
-    GR_TRY(fill_i32(minid, 0x7fffffff, n, st));
-    hipLaunchKernelGGL(k_min_member, dim3(gb), dim3(kT), 0, st, root, ids, n, minid);
-    GR_LAUNCHED("min member");
-    int32_t* flag_by_id = own;   // reuse
-    int32_t* rank_by_id = acc;   // reuse (acc no longer needed)
-    hipLaunchKernelGGL(k_leader_flags, dim3(gb), dim3(kT), 0, st, root, ids, minid, n, flag_by_id);
-    GR_LAUNCHED("leader flags");
-    GR_TRY(scan_exclusive_i32(flag_by_id, rank_by_id, n, small + 1, ws, st));
-    hipLaunchKernelGGL(k_assign, dim3(gb), dim3(kT), 0, st, root, minid, rank_by_id, n, agg);
-    GR_LAUNCHED("assign");
-    int32_t nc = 0;
-    GR_HIP(hipMemcpyAsync(&nc, small + 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
     *n_coarse = nc;
     ws.used = mark;
     return GR_OK;
@@ -880,15 +878,13 @@ static int hub_runs(const int32_t* blist, int32_t nbig, const int32_t* boff, int
                        (const uint32_t*)bv1, (const int32_t*)head, (int64_t)mb, piece);
     GR_LAUNCHED("segment tiles");
     int32_t bruns = 0;
-    GR_HIP(hipMemcpyAsync(&bruns, small + 9, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{small + 9, sizeof(int32_t)}}, &bruns, st));
     // each long segment's first run: the run keys' segment bits
     KT* rkey = bk0;  // free again
     hipLaunchKernelGGL(k_gather_keys<KT>, dim3(blocks_for(bruns, kT)), dim3(kT), 0, st,
                        (const KT*)bk1, (const uint32_t*)start, (int64_t)bruns, rkey);
     GR_LAUNCHED("run keys");
-    GR_TRY(fill_i32(bfirst, -1, nbig, st));
-    GR_TRY(fill_i32(bend, -1, nbig, st));
+    GR_TRY(fill_many({{bfirst, -1, nbig}, {bend, -1, nbig}}, st));
     hipLaunchKernelGGL(k_row_bounds<KT>, dim3(blocks_for(bruns, kT)), dim3(kT), 0, st,
                        (const KT*)rkey, (int64_t)bruns, jbits, bfirst, bend);
     GR_LAUNCHED("long segment run bounds");
@@ -965,15 +961,15 @@ int galerkin(const gr_graph* g, const int32_t* agg, int64_t n_c, int32_t* c_row_
                        (const int32_t*)rcnt, n, cnt_s, tpos);
     GR_LAUNCHED("sorted counts");
     GR_TRY(scan_exclusive_i32(cnt_s, pos_s, n, pos_s + n, ws, st));
-    GR_TRY(fill_i32(small, 0, 16, st));
-    GR_TRY(fill_i32(afirst, -1, n_c, st));
+    GR_TRY(fill_many({{small, 0, 16}, {afirst, -1, n_c}, {lfirst, -1, n_c + 1}, {lend, -1, n_c + 1},
+                      {rc, 0, n_c}}, st));
     hipLaunchKernelGGL(k_agg_bounds, dim3(nb), dim3(kT), 0, st, (const uint32_t*)skey, n, afirst,
                        aend);
     GR_LAUNCHED("aggregate row bounds");
-    // the class of every coarse row (rc holds it until the runs are counted)
+    // the class of every coarse row (roff holds it until the runs are counted)
     hipLaunchKernelGGL(k_agg_segments, dim3(blocks_for(n_c, kT)), dim3(kT), 0, st,
                        (const int32_t*)afirst, (const int32_t*)aend, (const int32_t*)pos_s, n_c, uoff,
-                       ucnt, rc);
+                       ucnt, roff);
     GR_LAUNCHED("aggregate segments");
     // the rows of each class in row order, classes one after another
     {
@@ -982,11 +978,11 @@ int galerkin(const gr_graph* g, const int32_t* agg, int64_t n_c, int32_t* c_row_
         int32_t* bcnt = ws.take<int32_t>((size_t)kGalClasses * nblk + 1);
         int32_t* boffs = ws.take<int32_t>((size_t)kGalClasses * nblk + 1);
         if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (galerkin classes)");
-        hipLaunchKernelGGL(k_class_counts, dim3(nblk), dim3(kT), 0, st, (const int32_t*)rc, n_c, nblk,
+        hipLaunchKernelGGL(k_class_counts, dim3(nblk), dim3(kT), 0, st, (const int32_t*)roff, n_c, nblk,
                            bcnt);
         GR_LAUNCHED("class counts");
         GR_TRY(scan_exclusive_i32(bcnt, boffs, (int64_t)kGalClasses * nblk, nullptr, ws, st));
-        hipLaunchKernelGGL(k_class_scatter, dim3(nblk), dim3(kT), 0, st, (const int32_t*)rc, n_c, nblk,
+        hipLaunchKernelGGL(k_class_scatter, dim3(nblk), dim3(kT), 0, st, (const int32_t*)roff, n_c, nblk,
                            (const int32_t*)boffs, lists);
         GR_LAUNCHED("class lists");
         hipLaunchKernelGGL(k_class_starts, dim3(1), dim3(kWave), 0, st, (const int32_t*)boffs, nblk,
@@ -994,13 +990,9 @@ int galerkin(const gr_graph* g, const int32_t* agg, int64_t n_c, int32_t* c_row_
         GR_LAUNCHED("class starts");
         ws.used = mk;  // stream order keeps them valid for the launches above
     }
-    int32_t cs[kGalClasses + 1] = {0};  // class starts in the list
-    GR_HIP(hipMemcpyAsync(cs, small, sizeof(int32_t) * (kGalClasses + 1), hipMemcpyDeviceToHost, st));
-    int32_t m = 0;
-    GR_HIP(hipMemcpyAsync(&m, pos_s + n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
-    GR_TRY(fill_i32(lfirst, -1, n_c + 1, st));
-    GR_TRY(fill_i32(lend, -1, n_c + 1, st));
+    int32_t cs[kGalClasses + 2] = {0};  // class starts in the list, and the kept entries
+    GR_TRY(fetch({{small, sizeof(int32_t) * (kGalClasses + 1)}, {pos_s + n, sizeof(int32_t)}}, cs, st));
+    const int32_t m = cs[kGalClasses + 1];
     if (m == 0) {
         GR_TRY(fill_i32(c_row_ptr, 0, n_c + 1, st));
         ws.used = mark;
@@ -1029,7 +1021,6 @@ int galerkin(const gr_graph* g, const int32_t* agg, int64_t n_c, int32_t* c_row_
                            g->w, agg, long_rows, (const int32_t*)tpos, (const int32_t*)pos_s, ej, ew);
         GR_LAUNCHED("place rows (long)");
     }
-    GR_TRY(fill_i32(rc, 0, n_c, st));
     // each segment collapsed into its runs
     auto cls_n = [&](int k) { return cs[k + 1] - cs[k]; };
     auto cls_list = [&](int k) { return (const int32_t*)(lists + cs[k]); };
@@ -1078,8 +1069,7 @@ int galerkin(const gr_graph* g, const int32_t* agg, int64_t n_c, int32_t* c_row_
         GR_LAUNCHED("long segment sizes");
         GR_TRY(scan_exclusive_i32(bsz, boff, nbig, small + 8, ws, st));
         int32_t mb = 0;
-        GR_HIP(hipMemcpyAsync(&mb, small + 8, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        GR_HIP(hipStreamSynchronize(st));
+        GR_TRY(fetch({{small + 8, sizeof(int32_t)}}, &mb, st));
         // keys (segment rank << jbits | J) of 32 bits where they fit
         const int bbits = bits_for(nbig);
         if (bbits + jbits <= 32)
@@ -1107,8 +1097,7 @@ int galerkin(const gr_graph* g, const int32_t* agg, int64_t n_c, int32_t* c_row_
         GR_TRY(scan_exclusive_i32(hrc, hoff, nh, small + 11, ws, st));
     }
     int32_t tot[2] = {0, 0};  // runs, runs of the long rows
-    GR_HIP(hipMemcpyAsync(tot, small + 10, sizeof(tot), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{small + 10, sizeof(tot)}}, tot, st));
     const int32_t runs = tot[0];
     const int32_t hr = nh > 0 ? tot[1] : 0;
     uint64_t* ukey = ws.take<uint64_t>(runs);

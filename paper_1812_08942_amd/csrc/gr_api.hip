@@ -99,10 +99,11 @@ __global__ void k_map_ids(const int32_t* __restrict__ in, const int32_t* __restr
     if (i < n) out[i] = perm[in[i]];
 }
 
-// total[v] = lvl[total[v]]
-__global__ void k_compose(const int32_t* __restrict__ lvl, int64_t n0, int32_t* __restrict__ total) {
+// total[v] = lvl[total[v]], lvl itself for the first level
+__global__ void k_compose(const int32_t* __restrict__ lvl, int64_t n0, int first,
+                          int32_t* __restrict__ total) {
     int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n0) total[v] = lvl[total[v]];
+    if (v < n0) total[v] = lvl[first ? v : total[v]];
 }
 
 // strongest neighbour from per-entry algebraic distances: argmin (d, j),
@@ -213,9 +214,8 @@ int gr_smooth(const gr_graph* g, const int32_t* colours, int32_t n_colours, int3
     GR_TRY(check_aligned(X, "X"));
     hipStream_t st = S(stream);
     Arena A(ws, ws_bytes);
-    GR_TRY(validate_colouring(g, colours, n_colours, A, st));
     OrderedGraph og;
-    GR_TRY(order_by_colour(g, colours, n_colours, &og, A, st));
+    GR_TRY(order_by_colour(g, colours, n_colours, true, &og, A, st));
     // permute X into colour-major rows, smooth, permute back
     size_t vb = vec_bytes(g->n, K, dtype);
     char* Xp = A.take<char>(vb);
@@ -346,10 +346,6 @@ static int reduce_impl(const gr_graph* g, const gr_params* p_in, gr_result* res,
     int32_t* gbuf_col[2] = {A.take<int32_t>(g->nnz + 1), A.take<int32_t>(g->nnz + 1)};
     float* gbuf_w[2] = {A.take<float>(g->nnz + 1), A.take<float>(g->nnz + 1)};
     if (A.overflow) return set_error(GR_ENOMEM, "workspace too small (%zu bytes given)", ws_bytes);
-    if (n0 > 0) {
-        hipLaunchKernelGGL(k_iota_i32, dim3(blocks_for(n0, 256)), dim3(256), 0, st, res->agg, n0);
-        GR_LAUNCHED("iota");
-    }
     gr_graph cur = *g;
     int which = 0;
     int level = 0;
@@ -364,8 +360,8 @@ static int reduce_impl(const gr_graph* g, const gr_params* p_in, gr_result* res,
         const bool pr = prof::on();
         const double xs = p.vec_dtype == GR_BF16 ? 2.0 : 4.0;
         if (pr) prof::begin(st);
-        if (level == 0 && p.colours) {
-            GR_TRY(validate_colouring(&cur, p.colours, p.n_colours, A, st));
+        const bool given = level == 0 && p.colours;
+        if (given) {
             col_use = p.colours;
             nc = p.n_colours;
         } else {
@@ -379,7 +375,7 @@ static int reduce_impl(const gr_graph* g, const gr_params* p_in, gr_result* res,
         }
         OrderedGraph og;
         if (pr) prof::begin(st);
-        GR_TRY(order_by_colour(&cur, col_use, nc, &og, A, st));
+        GR_TRY(order_by_colour(&cur, col_use, nc, given, &og, A, st));
         if (pr) prof::end(st, prof::RELABEL, 0.0, 1);
         if (pr) prof::begin(st);
         GR_TRY(init_vectors(cur.n, p.K, vseed, p.vec_dtype, og.perm, X, A, st));
@@ -418,11 +414,17 @@ static int reduce_impl(const gr_graph* g, const gr_params* p_in, gr_result* res,
         }
         A.used = mark_own;  // stream order keeps them valid for the launches above
         if (pr) prof::end(st, prof::AGGREGATE, 0.0, 1);
+        // the last level writes into the caller's buffers
+        const bool stuck = ncoarse == cur.n;
+        const bool last = stuck || ncoarse <= target || (p.max_levels > 0 && level + 1 >= p.max_levels);
+        int32_t* out_rp = last ? res->c_row_ptr : gbuf_rp[which];
+        int32_t* out_col = last ? res->c_col : gbuf_col[which];
+        float* out_w = last ? res->c_w : gbuf_w[which];
         gr_graph next;
         next.n = ncoarse;
-        next.row_ptr = gbuf_rp[which];
-        next.col = gbuf_col[which];
-        next.w = gbuf_w[which];
+        next.row_ptr = out_rp;
+        next.col = out_col;
+        next.w = out_w;
         int64_t nnzc = 0;
         if (pr) prof::begin(st);
         // the collapse runs on the level's graph in its own order, where an
@@ -436,14 +438,13 @@ static int reduce_impl(const gr_graph* g, const gr_params* p_in, gr_result* res,
                                og.long_rows, og.perm, og.n_long, long_own);
             GR_LAUNCHED("long rows, own order");
         }
-        GR_TRY(galerkin(&cur, aggl, ncoarse, gbuf_rp[which], gbuf_col[which], gbuf_w[which], &nnzc,
-                        long_own, og.n_long, A, st));
+        GR_TRY(galerkin(&cur, aggl, ncoarse, out_rp, out_col, out_w, &nnzc, long_own, og.n_long, A,
+                        st));
         if (pr) prof::end(st, prof::GALERKIN, 0.0, 1);
         next.nnz = nnzc;
         hipLaunchKernelGGL(k_compose, dim3(blocks_for(n0, 256)), dim3(256), 0, st, aggl, n0,
-                           res->agg);
+                           level == 0 ? 1 : 0, res->agg);
         GR_LAUNCHED("compose");
-        bool stuck = ncoarse == cur.n;
         if (hier && !stuck) {  // keep this level's map and the graph it made
             const int l = hier->levels;
             if (l >= GR_MAX_LEVELS) return set_error(GR_ENOMEM, "more than %d levels", GR_MAX_LEVELS);
@@ -483,13 +484,19 @@ static int reduce_impl(const gr_graph* g, const gr_params* p_in, gr_result* res,
             break;
         }
     }
-    // final coarse graph into the caller's buffers
-    GR_HIP(hipMemcpyAsync(res->c_row_ptr, cur.row_ptr, sizeof(int32_t) * (cur.n + 1),
-                          hipMemcpyDeviceToDevice, st));
-    if (cur.nnz > 0) {
-        GR_HIP(hipMemcpyAsync(res->c_col, cur.col, sizeof(int32_t) * cur.nnz, hipMemcpyDeviceToDevice,
-                              st));
-        GR_HIP(hipMemcpyAsync(res->c_w, cur.w, sizeof(float) * cur.nnz, hipMemcpyDeviceToDevice, st));
+    if (level == 0) {  // nothing to reduce: the identity and the graph itself
+        if (n0 > 0) {
+            hipLaunchKernelGGL(k_iota_i32, dim3(blocks_for(n0, 256)), dim3(256), 0, st, res->agg, n0);
+            GR_LAUNCHED("iota");
+        }
+        GR_HIP(hipMemcpyAsync(res->c_row_ptr, cur.row_ptr, sizeof(int32_t) * (cur.n + 1),
+                              hipMemcpyDeviceToDevice, st));
+        if (cur.nnz > 0) {
+            GR_HIP(hipMemcpyAsync(res->c_col, cur.col, sizeof(int32_t) * cur.nnz,
+                                  hipMemcpyDeviceToDevice, st));
+            GR_HIP(hipMemcpyAsync(res->c_w, cur.w, sizeof(float) * cur.nnz, hipMemcpyDeviceToDevice,
+                                  st));
+        }
     }
     res->n_coarse = cur.n;
     res->nnz_coarse = cur.nnz;

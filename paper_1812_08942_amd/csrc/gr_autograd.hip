@@ -83,8 +83,7 @@ int edge_list(const gr_graph* g, int32_t* eu, int32_t* ev, int32_t* eoe, int64_t
                        ev, eoe);
     GR_LAUNCHED("edge fill");
     int32_t E = 0;
-    GR_HIP(hipMemcpyAsync(&E, pos + g->nnz, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{pos + g->nnz, sizeof(int32_t)}}, &E, st));
     *n_edges = E;
     ws.used = mark;
     return GR_OK;
@@ -974,9 +973,8 @@ int smooth_vjp(const gr_graph* g, const int32_t* eoe, int64_t E, const int32_t* 
                int32_t K, int32_t S, int32_t dtype, const void* X0, const float* Gc, float* gw,
                float* gX0, int32_t store, Arena& ws, hipStream_t st) {
     const int64_t n = g->n, nnz = g->nnz;
-    GR_TRY(validate_colouring(g, colours, C, ws, st));
     OrderedGraph og;
-    GR_TRY(order_by_colour(g, colours, C, &og, ws, st));
+    GR_TRY(order_by_colour(g, colours, C, true, &og, ws, st));
     // weighted degrees, long-row pieces
     const int G = lanes_per_row(n, nnz);
     float* dw = ws.take<float>(n + 1);
@@ -1009,8 +1007,7 @@ int smooth_vjp(const gr_graph* g, const int32_t* eoe, int64_t E, const int32_t* 
     hipLaunchKernelGGL(k_gather_i32, dim3(blocks_for(2 * C + 1, 256)), dim3(256), 0, st,
                        (const int32_t*)ppos, (const int64_t*)pidx, (int64_t)(2 * C + 1), pbounds);
     GR_LAUNCHED("piece bounds");
-    GR_HIP(hipMemcpyAsync(hpb.data(), pbounds, sizeof(int32_t) * hpb.size(), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{pbounds, sizeof(int32_t) * hpb.size()}}, hpb.data(), st));
     const int64_t n_pieces = hpb[2 * C];
     VjpPlan pl;
     pl.og = &og;

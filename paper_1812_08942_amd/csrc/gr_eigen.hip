@@ -24,6 +24,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <vector>
 
 namespace gr {
@@ -750,9 +751,10 @@ static int run_chebyshev(Eig& s, int n_eig, int m, double b, double bf, double t
         std::swap(s.S, s.T);
         std::swap(s.LS, s.U);
         GR_TRY(s.residuals(s.LS, s.S, m));
-        GR_HIP(hipMemcpyAsync(th.data(), s.theta, sizeof(double) * m, hipMemcpyDeviceToHost, st));
-        GR_HIP(hipMemcpyAsync(rs.data(), s.res, sizeof(double) * m, hipMemcpyDeviceToHost, st));
-        GR_HIP(hipStreamSynchronize(st));
+        double ts[2 * kMaxP];
+        GR_TRY(fetch({{s.theta, sizeof(double) * m}, {s.res, sizeof(double) * m}}, ts, st));
+        std::copy(ts, ts + m, th.begin());
+        std::copy(ts + m, ts + 2 * m, rs.begin());
         worst = 0.0;
         for (int i = 0; i < n_eig && i < m; ++i) worst = fmax(worst, sqrt(fmax(rs[i], 0.0)));
         if (worst <= tol * b || m >= n - 1 || it >= max_iter) break;
@@ -806,9 +808,10 @@ static int run_lobpcg(Eig& s, int n_eig, int m, double b, double tol, int max_it
     worst = INFINITY;
     for (it = 0;; ++it) {
         GR_TRY(s.residuals(s.LS, s.S, m));
-        GR_HIP(hipMemcpyAsync(th.data(), s.theta, sizeof(double) * m, hipMemcpyDeviceToHost, st));
-        GR_HIP(hipMemcpyAsync(rs.data(), s.res, sizeof(double) * m, hipMemcpyDeviceToHost, st));
-        GR_HIP(hipStreamSynchronize(st));
+        double ts[2 * kMaxP];
+        GR_TRY(fetch({{s.theta, sizeof(double) * m}, {s.res, sizeof(double) * m}}, ts, st));
+        std::copy(ts, ts + m, th.begin());
+        std::copy(ts + m, ts + 2 * m, rs.begin());
         worst = 0.0;
         for (int i = 0; i < n_eig; ++i) worst = fmax(worst, sqrt(fmax(rs[i], 0.0)));
         if (worst <= tol * b || it >= max_iter) break;
@@ -824,8 +827,7 @@ static int run_lobpcg(Eig& s, int n_eig, int m, double b, double tol, int max_it
         GR_TRY(s.orthonormalise(s.S, p));
         if (have_p) {
             int flag = 0;
-            GR_HIP(hipMemcpyAsync(&flag, s.flag, sizeof(int), hipMemcpyDeviceToHost, st));
-            GR_HIP(hipStreamSynchronize(st));
+            GR_TRY(fetch({{s.flag, sizeof(int)}}, &flag, st));
             if (flag) {  // drop P and start the basis again from [X W]
                 ++restarts;
                 std::swap(s.S, s.U);
@@ -929,8 +931,7 @@ static int setup_operator(Eig& s, Arena& ws) {
     hipLaunchKernelGGL(k_lap_long_list, dim3(nb), dim3(kE), 0, st, g->row_ptr, (const int32_t*)pos,
                        n, s.long_rows);
     GR_LAUNCHED("long rows");
-    GR_HIP(hipMemcpyAsync(&s.n_long, pos + n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{pos + n, sizeof(int32_t)}}, &s.n_long, st));
     ws.used = mark;
     return GR_OK;
 }
@@ -979,8 +980,7 @@ int laplacian_eigs(const gr_graph* g, const double* bdiag, int32_t n_eig, int32_
         }
     }
     double dstat[2 + kBoundSteps];
-    GR_HIP(hipMemcpyAsync(dstat, s.small, sizeof(dstat), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{s.small, sizeof(dstat)}}, dstat, st));
     double b = 2.0 * dstat[0] * (1.0 + 1e-12) + 1e-300;  // lambda_max <= 2 max degree
     double bf = b;
     if (!bdiag)

@@ -6,6 +6,7 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <initializer_list>
 #include <vector>
 
 #include "graphreduce.h"
@@ -114,6 +115,27 @@ int sum_f64(const double* in, int64_t n, double* out, Arena& ws, hipStream_t st)
 
 int fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st);
 
+// Several fills in one launch; the ranges must not overlap.
+struct FillSpan {
+    int32_t* p;
+    int32_t v;
+    int64_t n;
+};
+int fill_many(std::initializer_list<FillSpan> spans, hipStream_t st);
+
+// Device words to the host, once everything before on the stream is done:
+// the spans one after another into out (each a whole number of 4-byte words).
+// A small kernel writes them and a flag into pinned host memory, which the
+// host watches: 6 us where a copy to pageable memory and a synchronisation
+// take 23.  The pages (64 KiB, at most 16 per process) are taken from a pool
+// for the length of the call and returned; larger transfers, and calls that
+// find no page, copy and synchronise.
+struct FetchSpan {
+    const void* src;
+    size_t bytes;
+};
+int fetch(std::initializer_list<FetchSpan> spans, void* out, hipStream_t st);
+
 inline int bits_for(int64_t n) {  // bits needed to hold values in [0, n)
     int b = 0;
     while (b < 63 && (int64_t(1) << b) < n) ++b;
@@ -124,8 +146,6 @@ inline int bits_for(int64_t n) {  // bits needed to hold values in [0, n)
 int validate_graph(const gr_graph* g, Arena& ws, hipStream_t st);
 int colour_greedy(const gr_graph* g, uint64_t seed, int ldf, int32_t* colours,
               int32_t* n_colours_host, Arena& ws, hipStream_t st);
-int validate_colouring(const gr_graph* g, const int32_t* colours, int32_t n_colours,
-                       Arena& ws, hipStream_t st);
 
 // Colour-major relabel: new row r holds old node perm[r]; rows of colour c
 // are [class_ptr[c], class_ptr[c+1]), and inside a class the rows come in
@@ -158,7 +178,9 @@ struct OrderedGraph {
     int32_t* long_rows;  // device [n_long]: their relabelled ids
     double mean_deg;
 };
-int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours,
+// check: whether the colouring comes from outside and has to be looked over
+// (GR_ECOLOUR for a colour out of range or an edge inside a colour)
+int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours, bool check,
                     OrderedGraph* out, Arena& ws, hipStream_t st);
 
 // dst[r] = src[perm[r]] (inverse = 0) or dst[perm[r]] = src[r] (inverse = 1),

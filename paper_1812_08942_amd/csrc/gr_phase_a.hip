@@ -65,8 +65,7 @@ int validate_graph(const gr_graph* g, Arena& ws, hipStream_t st) {
                        g->row_ptr, g->n, g->nnz, bad);
     GR_LAUNCHED("check row_ptr");
     int32_t hb = 0;
-    GR_HIP(hipMemcpyAsync(&hb, bad, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{bad, sizeof(int32_t)}}, &hb, st));
     if (hb) return set_error(GR_ECSR, "row_ptr is not a monotone offset array with row_ptr[0]=0, row_ptr[n]=nnz");
     if (g->n > 0) {
         int G = g->nnz < 8 * g->n ? 1 : 4;
@@ -74,8 +73,7 @@ int validate_graph(const gr_graph* g, Arena& ws, hipStream_t st) {
         hipLaunchKernelGGL(k_check_entries, dim3(blocks_for(g->n * G, kThreads)), dim3(kThreads), 0,
                            st, g->row_ptr, g->col, g->w, g->n, G, bad);
         GR_LAUNCHED("check entries");
-        GR_HIP(hipMemcpyAsync(&hb, bad, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        GR_HIP(hipStreamSynchronize(st));
+        GR_TRY(fetch({{bad, sizeof(int32_t)}}, &hb, st));
     }
     if (hb & 2) return set_error(GR_ECSR, "column index out of range or self-loop");
     if (hb & 4) return set_error(GR_ECSR, "columns not strictly increasing within a row");
@@ -105,11 +103,6 @@ __device__ inline int32_t first_free4(const uint64_t used[4], int32_t base) {
     for (int w = 0; w < 4; ++w)
         if (~used[w]) return base + w * 64 + __ffsll((unsigned long long)~used[w]) - 1;
     return -1;
-}
-
-__global__ void k_col_fill(int64_t n, int32_t* __restrict__ colours) {
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n) colours[v] = -1;
 }
 
 // ------------------------------------------------ colouring as a dataflow
@@ -166,7 +159,8 @@ __global__ void k_max_degree(const int32_t* __restrict__ rp, int64_t n, int32_t*
     for (; i < n; i += (int64_t)gridDim.x * blockDim.x) m = max(m, rp[i + 1] - rp[i]);
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, kWave));
-    if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(out, m);
+    // read first: same-address atomics serialise (256 blocks of them took 14 us)
+    if ((threadIdx.x & (kWave - 1)) == 0 && m > ld_dev(out)) atomicMax(out, m);
 }
 
 // bits of the largest degree (at least 1)
@@ -599,7 +593,7 @@ __global__ void __launch_bounds__(kThreads) k_flow_colours(const int32_t* __rest
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < kThreads / kWave; ++w) m = max(m, wm[w]);
-        atomicMax(mx, m);
+        if (m > ld_dev(mx)) atomicMax(mx, m);
     }
 }
 
@@ -674,8 +668,7 @@ static int colour_flow(const gr_graph* g, uint64_t seed, int ldf, int32_t* colou
     const char* plain_env = getenv("GR_COLOUR_PLAIN_LAUNCH");
     const bool plain = plain_env && plain_env[0] == '1';
     {
-        GR_HIP(hipMemsetAsync(small, 0, sizeof(int32_t) * 8, st));
-        GR_HIP(hipMemsetAsync(small + 4, 0xff, sizeof(int32_t), st));
+        GR_TRY(fill_many({{small, 0, 4}, {small + 4, -1, 1}, {small + 5, 0, 3}, {cpos, -1, n}}, st));
         hipLaunchKernelGGL(k_max_degree, dim3(256), dim3(kThreads), 0, st, g->row_ptr, n, small);
         GR_LAUNCHED("colour max degree");
         // the priority order
@@ -720,8 +713,6 @@ static int colour_flow(const gr_graph* g, uint64_t seed, int ldf, int32_t* colou
         hipLaunchKernelGGL(k_flow_batches, dim3(ngb), dim3(kThreads), 0, st, (const int32_t*)pcnt,
                            n, (const int32_t*)boff, batches);
         GR_LAUNCHED("colour batches");
-        hipLaunchKernelGGL(k_col_fill, dim3(nb), dim3(kThreads), 0, st, n, cpos);
-        GR_LAUNCHED("colour fill");
         // on graphs with hubs the first positions in one workgroup; the flow
         // then starts at the batch the core kernel leaves in small[6]
         hipLaunchKernelGGL(k_jp_core, dim3(1), dim3(kCoreThreads), 0, st, (const int32_t*)pstart,
@@ -750,8 +741,7 @@ static int colour_flow(const gr_graph* g, uint64_t seed, int ldf, int32_t* colou
                            colours, small + 4);
         GR_LAUNCHED("colour gather");
         int32_t hs[8];
-        GR_HIP(hipMemcpyAsync(hs, small, sizeof(hs), hipMemcpyDeviceToHost, st));
-        GR_HIP(hipStreamSynchronize(st));
+        GR_TRY(fetch({{small, sizeof(hs)}}, hs, st));
         if (hs[3]) return set_error(GR_EHIP, "colouring wait timed out");
         if (hs[4] < 0) return set_error(GR_EHIP, "colouring left nodes uncoloured");
         *n_colours_host = hs[4] + 1;
@@ -782,25 +772,16 @@ __global__ void k_check_colouring(const int32_t* __restrict__ rp, const int32_t*
     if (f) atomicOr(bad, f);
 }
 
-int validate_colouring(const gr_graph* g, const int32_t* colours, int32_t n_colours, Arena& ws,
-                       hipStream_t st) {
+// flags of what is wrong with a colouring into *bad (zero before)
+static int check_colouring(const gr_graph* g, const int32_t* colours, int32_t n_colours, int32_t* bad,
+                           hipStream_t st) {
     if (g->n == 0) return GR_OK;
-    size_t mark = ws.used;
-    int32_t* bad = ws.take<int32_t>(1);
-    if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small");
-    GR_HIP(hipMemsetAsync(bad, 0, sizeof(int32_t), st));
     // one lane per row below a mean degree of 8, else about half the mean degree
     int G = g->nnz < 8 * g->n ? 1 : 4;
     while (G > 1 && G < kWave && G * 2 <= g->nnz / g->n) G *= 2;
     hipLaunchKernelGGL(k_check_colouring, dim3(blocks_for(g->n * G, kThreads)), dim3(kThreads), 0, st,
                        g->row_ptr, g->col, colours, g->n, n_colours, G, bad);
     GR_LAUNCHED("check colouring");
-    int32_t hb = 0;
-    GR_HIP(hipMemcpyAsync(&hb, bad, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
-    ws.used = mark;
-    if (hb & 1) return set_error(GR_ECOLOUR, "colour out of range [0, %d)", n_colours);
-    if (hb & 2) return set_error(GR_ECOLOUR, "an edge joins two nodes of one colour");
     return GR_OK;
 }
 
@@ -808,12 +789,15 @@ int validate_colouring(const gr_graph* g, const int32_t* colours, int32_t n_colo
 // Rows are relabelled by the key (colour, degree tier, old id): the rows of
 // one colour become a contiguous range, in decreasing degree tiers, so that
 // one smoothing launch can give every tier its own lanes-per-row.
+// (a colour out of range, which the check reports, goes with colour 0)
 __global__ void k_bucket_keys(const int32_t* __restrict__ rp, const int32_t* __restrict__ colours,
-                              int64_t n, uint32_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+                              int64_t n, int32_t n_colours, uint32_t* __restrict__ keys,
+                              uint32_t* __restrict__ vals) {
     int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n) return;
     int32_t deg = rp[v + 1] - rp[v];
-    uint32_t b = (uint32_t)colours[v] * kNT + (uint32_t)degree_tier(deg);
+    const int32_t c = colours[v];
+    uint32_t b = (uint32_t)(c >= 0 && c < n_colours ? c : 0) * kNT + (uint32_t)degree_tier(deg);
     keys[v] = b;
     vals[v] = (uint32_t)v;
 }
@@ -872,28 +856,29 @@ __global__ void k_perm_entries(const int32_t* __restrict__ rp, const int32_t* __
 // per bucket: rows, and stored entries (from the relabelled row pointers)
 __global__ void k_bucket_sizes(const int32_t* __restrict__ bfirst, const int32_t* __restrict__ bend,
                                const int32_t* __restrict__ nrp, int32_t nb,
-                               int64_t* __restrict__ out) {
+                               int32_t* __restrict__ out) {
     int32_t b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= nb) return;
     int32_t f = bfirst[b], e = bend[b];
-    out[2 * b] = f >= 0 ? (int64_t)(e - f) : 0;
-    out[2 * b + 1] = f >= 0 ? (int64_t)(nrp[e] - nrp[f]) : 0;
+    out[2 * b] = f >= 0 ? e - f : 0;
+    out[2 * b + 1] = f >= 0 ? nrp[e] - nrp[f] : 0;
 }
 
-// ids of the long rows, class by class: class c contributes the rows
-// [cls[2c], cls[2c] + cls[2c+1]) at offset off[c]
-__global__ void k_long_rows(const int64_t* __restrict__ cls, const int32_t* __restrict__ off,
-                            int32_t n_colours, int32_t* __restrict__ out) {
-    int32_t c = blockIdx.y;
-    if (c >= n_colours) return;
-    const int64_t first = cls[2 * c], cnt = cls[2 * c + 1];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt;
-         i += (int64_t)gridDim.x * blockDim.x)
-        out[off[c] + i] = (int32_t)(first + i);
+// ids of the long rows, class by class: the k-th of the classes at hand
+// contributes the rows [first[k], first[k] + cnt[k]) at offset off[k].  The
+// table travels with the launch.
+constexpr int kLongClasses = 256;
+struct LongClasses {
+    int32_t first[kLongClasses], cnt[kLongClasses], off[kLongClasses];
+};
+__global__ void k_long_rows(LongClasses c, int32_t* __restrict__ out) {
+    const int k = blockIdx.y;
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < c.cnt[k]; i += gridDim.x * blockDim.x)
+        out[c.off[k] + i] = c.first[k] + i;
 }
 
-int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours, OrderedGraph* og,
-                    Arena& ws, hipStream_t st) {
+int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours, bool check,
+                    OrderedGraph* og, Arena& ws, hipStream_t st) {
     const int64_t n = g->n, nnz = g->nnz;
     og->n_colours = n_colours;
     // the sort's two value buffers: the permutation ends in either
@@ -910,14 +895,14 @@ int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours
     uint32_t* k1 = ws.take<uint32_t>(n);
     int32_t* bfirst = ws.take<int32_t>(nb + 1);
     int32_t* bend = ws.take<int32_t>(nb + 1);
-    int64_t* sizes = ws.take<int64_t>(2 * (int64_t)nb + 2);
+    int32_t* sizes = ws.take<int32_t>(2 * (size_t)nb + 2);  // and the colouring's flags
     int32_t* deg = ws.take<int32_t>(n + 1);
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (relabel)");
-    GR_TRY(fill_i32(bfirst, -1, nb + 1, st));
-    GR_TRY(fill_i32(bend, -1, nb + 1, st));
+    GR_TRY(fill_many({{bfirst, -1, nb + 1}, {bend, -1, nb + 1}, {sizes + 2 * (size_t)nb, 0, 1}}, st));
+    if (check) GR_TRY(check_colouring(g, colours, n_colours, sizes + 2 * (size_t)nb, st));
     if (n > 0) {
         hipLaunchKernelGGL(k_bucket_keys, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st,
-                           g->row_ptr, colours, n, k0, v0);
+                           g->row_ptr, colours, n, n_colours, k0, v0);
         GR_LAUNCHED("bucket keys");
     }
     GR_TRY(radix_sort_pairs32(k0, v0, k1, perm, n, bits_for(nb), ws, st));
@@ -939,22 +924,22 @@ int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours
         GR_LAUNCHED("perm entries");
     }
     // bucket sizes (rows, entries) on the host
-    std::vector<int64_t> hs(2 * (size_t)nb);
+    std::vector<int32_t> hs(2 * (size_t)nb + 1);
     if (nb > 0) {
         hipLaunchKernelGGL(k_bucket_sizes, dim3(blocks_for(nb, kThreads)), dim3(kThreads), 0, st,
                            bfirst, bend, nrp, nb, sizes);
         GR_LAUNCHED("bucket sizes");
-        GR_HIP(hipMemcpyAsync(hs.data(), sizes, sizeof(int64_t) * 2 * nb, hipMemcpyDeviceToHost, st));
-        GR_HIP(hipStreamSynchronize(st));
+        GR_TRY(fetch({{sizes, sizeof(int32_t) * hs.size()}}, hs.data(), st));
     }
+    const int32_t bad = hs[2 * (size_t)nb];
+    if (bad & 1) return set_error(GR_ECOLOUR, "colour out of range [0, %d)", n_colours);
+    if (bad & 2) return set_error(GR_ECOLOUR, "an edge joins two nodes of one colour");
     og->class_ptr_h.assign((size_t)n_colours + 1, 0);
     og->tier_ptr_h.assign((size_t)nb + 1, 0);
     og->long_end_h.assign((size_t)n_colours, 0);
     og->class_nnz_h.assign((size_t)n_colours, 0);
     og->class_e_h.assign((size_t)n_colours + 1, 0);
     og->long_nnz_h.assign((size_t)n_colours, 0);
-    std::vector<int64_t> cls(2 * (size_t)n_colours + 2, 0);
-    std::vector<int32_t> long_off(n_colours + 1, 0);
     int64_t total = 0, nlong = 0;
     for (int c = 0; c < n_colours; ++c) {
         og->class_ptr_h[c] = total;
@@ -973,12 +958,8 @@ int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours
         og->class_e_h[c + 1] = og->class_e_h[c] + nz;
         og->long_nnz_h[c] = lz;
         og->long_end_h[c] = og->class_ptr_h[c] + lr;
-        cls[2 * c] = og->class_ptr_h[c];
-        cls[2 * c + 1] = lr;
-        long_off[c] = (int32_t)nlong;
         nlong += lr;
     }
-    long_off[n_colours] = (int32_t)nlong;
     og->class_ptr_h[n_colours] = total;
     og->tier_ptr_h[nb] = total;
     if (total != n) return set_error(GR_ECOLOUR, "colouring does not cover every node");
@@ -989,20 +970,20 @@ int order_by_colour(const gr_graph* g, const int32_t* colours, int32_t n_colours
     og->long_rows = nullptr;
     if (nlong > 0) {
         og->long_rows = ws.take<int32_t>(nlong);
-        const size_t keep = ws.used;
-        int32_t* loff = ws.take<int32_t>(n_colours + 1);
-        int64_t* dcls = ws.take<int64_t>(2 * (size_t)n_colours + 2);
         if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (long rows)");
-        GR_HIP(hipMemcpyAsync(loff, long_off.data(), sizeof(int32_t) * (n_colours + 1),
-                              hipMemcpyHostToDevice, st));
-        GR_HIP(hipMemcpyAsync(dcls, cls.data(), sizeof(int64_t) * 2 * n_colours,
-                              hipMemcpyHostToDevice, st));
-        hipLaunchKernelGGL(k_long_rows, dim3(8, n_colours), dim3(kThreads), 0, st,
-                           (const int64_t*)dcls, (const int32_t*)loff, n_colours, og->long_rows);
-        GR_LAUNCHED("long rows");
-        // the host vectors and the small tables are released below
-        GR_HIP(hipStreamSynchronize(st));
-        ws.used = keep;
+        int32_t off = 0;
+        for (int c0 = 0; c0 < n_colours; c0 += kLongClasses) {
+            LongClasses t{};
+            const int cn = std::min(kLongClasses, n_colours - c0);
+            for (int k = 0; k < cn; ++k) {
+                t.first[k] = (int32_t)og->class_ptr_h[c0 + k];
+                t.cnt[k] = (int32_t)(og->long_end_h[c0 + k] - og->class_ptr_h[c0 + k]);
+                t.off[k] = off;
+                off += t.cnt[k];
+            }
+            hipLaunchKernelGGL(k_long_rows, dim3(8, cn), dim3(kThreads), 0, st, t, og->long_rows);
+            GR_LAUNCHED("long rows");
+        }
     }
     og->g.n = n;
     og->g.nnz = nnz;

@@ -5,8 +5,11 @@
 
 #include <algorithm>
 
+#include <mutex>
+
 #include <stdarg.h>
 #include <stdio.h>
+#include <stdlib.h>
 #include <string.h>
 
 namespace gr {
@@ -672,6 +675,155 @@ int fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st) {
     if (n <= 0) return GR_OK;
     hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(n, 256)), dim3(256), 0, st, p, v, n);
     GR_LAUNCHED("fill");
+    return GR_OK;
+}
+
+constexpr int kFillSpans = 6;
+struct FillArgs {
+    FillSpan span[kFillSpans];
+    int count;
+};
+
+__global__ void k_fill_many(FillArgs a) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int k = 0; k < a.count; ++k) {
+        if (i < a.span[k].n) {
+            a.span[k].p[i] = a.span[k].v;
+            return;
+        }
+        i -= a.span[k].n;
+    }
+}
+
+int fill_many(std::initializer_list<FillSpan> spans, hipStream_t st) {
+    FillArgs a{};
+    int64_t total = 0;
+    for (const FillSpan& f : spans)
+        if (f.n > 0) {
+            if (a.count == kFillSpans) return set_error(GR_EINVAL, "too many fills at once");
+            a.span[a.count++] = f;
+            total += f.n;
+        }
+    if (total == 0) return GR_OK;
+    hipLaunchKernelGGL(k_fill_many, dim3(blocks_for(total, 256)), dim3(256), 0, st, a);
+    GR_LAUNCHED("fills");
+    return GR_OK;
+}
+
+// ------------------------------------------------------- words to the host
+constexpr size_t kPageBytes = 64 * 1024;
+constexpr size_t kPageData = kPageBytes - 64;  // the flag has a line of its own
+constexpr int kMaxPages = 16;
+constexpr int kFetchSpans = 4;
+
+struct Page {
+    char* host;
+    char* dev;
+    uint32_t seq;  // of the last transfer
+};
+
+namespace {
+std::mutex g_pages_mu;
+std::vector<Page> g_pages;  // free ones
+int g_pages_made = 0;
+
+void free_pages() {  // at exit; pages in use then stay
+    std::lock_guard<std::mutex> lock(g_pages_mu);
+    for (Page& q : g_pages) (void)hipHostFree(q.host);
+    g_pages.clear();
+}
+
+bool take_page(Page* out) {
+    std::lock_guard<std::mutex> lock(g_pages_mu);
+    if (!g_pages.empty()) {
+        *out = g_pages.back();
+        g_pages.pop_back();
+        return true;
+    }
+    if (g_pages_made == kMaxPages) return false;
+    void *h = nullptr, *d = nullptr;
+    if (hipHostMalloc(&h, kPageBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipHostFree(h);
+        return false;
+    }
+    if (g_pages_made++ == 0) std::atexit(free_pages);
+    memset(h, 0, kPageBytes);
+    *out = Page{(char*)h, (char*)d, 0};
+    return true;
+}
+
+void return_page(const Page& q) {
+    std::lock_guard<std::mutex> lock(g_pages_mu);
+    g_pages.push_back(q);
+}
+}  // namespace
+
+struct FetchArgs {
+    const uint32_t* src[kFetchSpans];
+    int32_t words[kFetchSpans];
+    int count;
+};
+
+__global__ void __launch_bounds__(256) k_fetch(FetchArgs a, uint32_t* out, uint32_t* flag,
+                                               uint32_t seq) {
+    for (int k = 0; k < a.count; ++k) {
+        for (int i = threadIdx.x; i < a.words[k]; i += 256)
+            __hip_atomic_store(out + i, a.src[k][i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        out += a.words[k];
+    }
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+int fetch(std::initializer_list<FetchSpan> spans, void* out, hipStream_t st) {
+    size_t total = 0;
+    for (const FetchSpan& f : spans) total += f.bytes;
+    Page q{};
+    if (total > kPageData || (int)spans.size() > kFetchSpans || !take_page(&q)) {
+        char* at = (char*)out;
+        for (const FetchSpan& f : spans) {
+            GR_HIP(hipMemcpyAsync(at, f.src, f.bytes, hipMemcpyDeviceToHost, st));
+            at += f.bytes;
+        }
+        GR_HIP(hipStreamSynchronize(st));
+        return GR_OK;
+    }
+    FetchArgs a{};
+    for (const FetchSpan& f : spans) {
+        a.src[a.count] = (const uint32_t*)f.src;
+        a.words[a.count++] = (int32_t)(f.bytes / 4);
+    }
+    const uint32_t seq = ++q.seq;
+    uint32_t* flag = (uint32_t*)(q.host + kPageData);
+    hipLaunchKernelGGL(k_fetch, dim3(1), dim3(256), 0, st, a, (uint32_t*)q.dev,
+                       (uint32_t*)(q.dev + kPageData), seq);
+    int rc = check_hip(hipGetLastError(), "words to the host");
+    // the stream is asked now and then: a failure before the kernel must not
+    // leave the host waiting
+    for (unsigned it = 1; rc == GR_OK && __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq; ++it) {
+        if (it % 16384 != 0) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        rc = check_hip(e, "words to the host");
+        if (rc == GR_OK && __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq)
+            rc = set_error(GR_EHIP, "words to the host: the stream ended without them");
+    }
+    if (rc != GR_OK) return rc;  // the page may still be written to: it is not used again
+    memcpy(out, q.host, total);
+    return_page(q);
     return GR_OK;
 }
 

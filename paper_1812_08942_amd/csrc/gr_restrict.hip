@@ -144,9 +144,7 @@ static int restrict_rows(const int32_t* agg, int64_t n, int64_t nc, int32_t d, c
     GR_LAUNCHED("piece counts");
     GR_TRY(scan_exclusive_i32(cnt, ppos, nc, ppos + nc, ws, st));
     int32_t hb[2] = {0, 0};
-    GR_HIP(hipMemcpyAsync(&hb[0], bad, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipMemcpyAsync(&hb[1], ppos + nc, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{bad, sizeof(int32_t)}, {ppos + nc, sizeof(int32_t)}}, hb, st));
     if (hb[0] & 1) return set_error(GR_EINVAL, "an aggregate id lies outside [0, %lld)", (long long)nc);
     if (hb[0] & 2) return set_error(GR_EINVAL, "an aggregate has no member");
     const int64_t np = hb[1];

@@ -810,10 +810,7 @@ struct Sgd {
     }
     double read(int slot) {
         double v = 0.0;
-        if (hipMemcpyAsync(&v, sc + slot, sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
-            return NAN;
-        if (hipStreamSynchronize(st) != hipSuccess) return NAN;
-        return v;
+        return fetch({{sc + slot, sizeof(double)}}, &v, st) == GR_OK ? v : NAN;
     }
     // y = L_P^+ b by preconditioned CG, b orthogonal to 1
     int solve(const double* b, double* out) {
@@ -889,8 +886,7 @@ struct Sgd {
         GR_TRY(dot(h, t1, n, SC_LAMN));
         // one read back: the scalars and the solves' status behind them
         double hs[SC_WORDS];
-        GR_HIP(hipMemcpyAsync(hs, sc, sizeof(hs), hipMemcpyDeviceToHost, st));
-        GR_HIP(hipStreamSynchronize(st));
+        GR_TRY(fetch({{sc, sizeof(hs)}}, hs, st));
         *lam = hs[SC_LAMN];
         if (lam1) *lam1 = hs[SC_LAM1];
         if (resident) {
@@ -1136,8 +1132,7 @@ static int count_flags(const int32_t* flags, int64_t E, int64_t* out, Arena& ws,
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (count)");
     GR_TRY(scan_exclusive_i32(flags, tmp, E, tot, ws, st));
     int32_t h = 0;
-    GR_HIP(hipMemcpyAsync(&h, tot, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{tot, sizeof(int32_t)}}, &h, st));
     *out = h;
     ws.used = mark;
     return GR_OK;
@@ -1166,8 +1161,7 @@ int spanning_forest(const gr_graph* g, const int32_t* eu, const int32_t* ev, con
                            ev, (const int32_t*)comp, n, nxt, in_tree, flag);
         GR_LAUNCHED("forest hook");
         int32_t hooked = 0;
-        GR_HIP(hipMemcpyAsync(&hooked, flag, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        GR_HIP(hipStreamSynchronize(st));
+        GR_TRY(fetch({{flag, sizeof(int32_t)}}, &hooked, st));
         if (!hooked) break;
         hipLaunchKernelGGL(k_bv_pairs, dim3(nb), dim3(kS), 0, st, nxt, n);
         GR_LAUNCHED("forest pairs");
@@ -1178,8 +1172,7 @@ int spanning_forest(const gr_graph* g, const int32_t* eu, const int32_t* ev, con
                 GR_LAUNCHED("forest jump");
             }
             int32_t moved = 0;
-            GR_HIP(hipMemcpyAsync(&moved, flag + 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-            GR_HIP(hipStreamSynchronize(st));
+            GR_TRY(fetch({{flag + 1, sizeof(int32_t)}}, &moved, st));
             if (!moved) break;
         }
         hipLaunchKernelGGL(k_bv_relabel, dim3(nb), dim3(kS), 0, st, comp, (const int32_t*)nxt, n);
@@ -1270,9 +1263,7 @@ int subgraph(const gr_graph* g, const int32_t* eoe, const int32_t* keep, int64_t
         GR_LAUNCHED("subgraph edges");
     }
     int32_t h[2] = {0, 0};
-    GR_HIP(hipMemcpyAsync(&h[0], prp + n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipMemcpyAsync(&h[1], tot, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    GR_HIP(hipStreamSynchronize(st));
+    GR_TRY(fetch({{prp + n, sizeof(int32_t)}, {tot, sizeof(int32_t)}}, h, st));
     *p_nnz = h[0];
     *p_edges = h[1];
     ws.used = mark;
