@@ -89,20 +89,30 @@ int validate_graph(const gr_graph* g, Arena& ws, hipStream_t st) {
 // Priority: (h(v), v), h(v) = splitmix64 output v of the colour seed, or
 // (deg(v), h(v), v) largest-degree-first.
 
-__device__ inline uint64_t wave_or(uint64_t x) {
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        uint32_t lo = __shfl_xor((uint32_t)x, off, kWave);
-        uint32_t hi = __shfl_xor((uint32_t)(x >> 32), off, kWave);
-        x |= ((uint64_t)hi << 32) | lo;
-    }
-    return x;
+// The colours seen by a wave, as 256 bits in LDS of its own.  The lanes set
+// their bits as the colours arrive, so that after the last one only a read is
+// left of what a dependent node waits for (an or over the wave's lanes took
+// 24 cross-lane moves at that point).  A wave's LDS operations are in order.
+constexpr int kMaskWords = 8;
+__device__ inline void mask_clear(uint32_t* mask) {
+    const int lane = threadIdx.x & (kWave - 1);
+    if (lane < kMaskWords)
+        __hip_atomic_store(mask + lane, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-
-__device__ inline int32_t first_free4(const uint64_t used[4], int32_t base) {
-    for (int w = 0; w < 4; ++w)
-        if (~used[w]) return base + w * 64 + __ffsll((unsigned long long)~used[w]) - 1;
-    return -1;
+__device__ inline void mask_set(uint32_t* mask, int32_t c) {
+    if (c >= 0 && c < 32 * kMaskWords)
+        __hip_atomic_fetch_or(mask + (c >> 5), 1u << (c & 31), __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// the smallest colour not set, -1 if all are
+__device__ inline int32_t mask_first_free(const uint32_t* mask) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t w = ~__hip_atomic_load(mask + (lane & (kMaskWords - 1)), __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint64_t some = __ballot(w != 0) & ((1ull << kMaskWords) - 1);
+    if (!some) return -1;
+    const int k = __ffsll((unsigned long long)some) - 1;
+    return 32 * k + __ffs((int)__builtin_amdgcn_readlane((int)w, k)) - 1;
 }
 
 // ------------------------------------------------ colouring as a dataflow
@@ -303,9 +313,9 @@ __global__ void __launch_bounds__(kThreads) k_flow_count_wide(
 // one position with the whole wave; false when the wave must leave (abort)
 __device__ inline bool flow_wide(const int32_t* __restrict__ uplist, int32_t s, int32_t m,
                                  int64_t i, int32_t* cpos, int32_t* abort_flag,
-                                 unsigned spin_limit) {
+                                 unsigned spin_limit, uint32_t* mask) {
     const int lane = threadIdx.x & (kWave - 1);
-    uint64_t used[4] = {0, 0, 0, 0};
+    mask_clear(mask);
     int stop = 0;
     for (int32_t b = lane; b < m && !stop; b += kWave * kFlowU) {
         int32_t u[kFlowU], c[kFlowU];
@@ -332,38 +342,34 @@ __device__ inline bool flow_wide(const int32_t* __restrict__ uplist, int32_t s, 
             }
         }
 #pragma unroll
-        for (int k = 0; k < kFlowU; ++k)
-            if (c[k] >= 0 && c[k] < 256) used[c[k] >> 6] |= 1ull << (c[k] & 63);
+        for (int k = 0; k < kFlowU; ++k) mask_set(mask, c[k]);
     }
     if (__ballot(stop)) return false;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) used[w] = wave_or(used[w]);
-    int32_t c = first_free4(used, 0);
+    int32_t c = mask_first_free(mask);
     // colours 0..255 all taken: later windows (every listed neighbour is
     // coloured by now); colour <= m ends the search
     for (int32_t base = 256; c < 0; base += 256) {
-        uint64_t wu[4] = {0, 0, 0, 0};
-        for (int32_t e = lane; e < m; e += kWave) {
-            const int32_t cj = ld_dev(cpos + uplist[s + e]);
-            if (cj >= base && cj < base + 256) wu[(cj - base) >> 6] |= 1ull << ((cj - base) & 63);
-        }
-#pragma unroll
-        for (int w = 0; w < 4; ++w) wu[w] = wave_or(wu[w]);
-        c = first_free4(wu, base);
+        mask_clear(mask);
+        for (int32_t e = lane; e < m; e += kWave) mask_set(mask, ld_dev(cpos + uplist[s + e]) - base);
+        c = mask_first_free(mask);
+        if (c >= 0) c += base;
     }
     if (lane == 0) st_dev(cpos + i, c);
     return true;
 }
 
-// or over the aligned group of kFlowG lanes (every lane of the wave calls it)
+// or over the aligned group of kFlowG lanes (every lane of the wave calls
+// it), by cross-lane operands of the vector unit: lane ^ 1, lane ^ 2, the
+// mirrored 8
+template <int CTRL>
+__device__ inline uint32_t dpp_or(uint32_t x) {
+    return x | (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xf, 0xf, false);
+}
 __device__ inline uint64_t group_or(uint64_t x) {
-#pragma unroll
-    for (int off = 1; off < kFlowG; off <<= 1) {
-        uint32_t lo = __shfl_xor((uint32_t)x, off, kWave);
-        uint32_t hi = __shfl_xor((uint32_t)(x >> 32), off, kWave);
-        x |= ((uint64_t)hi << 32) | lo;
-    }
-    return x;
+    static_assert(kFlowG == 8, "three steps");
+    const uint32_t lo = dpp_or<0x141>(dpp_or<0x4E>(dpp_or<0xB1>((uint32_t)x)));
+    const uint32_t hi = dpp_or<0x141>(dpp_or<0x4E>(dpp_or<0xB1>((uint32_t)(x >> 32))));
+    return ((uint64_t)hi << 32) | lo;
 }
 
 // kFlowBatch positions together, kFlowG lanes each, every position with at
@@ -457,6 +463,9 @@ __global__ void k_flow_batches(const int32_t* __restrict__ pcnt, int64_t n,
 // across the chip.  Waves take positions w, w + 16, ... in order, a whole
 // wave per position; the deadlock argument of the device-wide flow holds
 // inside the workgroup, and every wait is bounded the same way.
+#ifndef GR_CORE_SLEEP
+#define GR_CORE_SLEEP 1
+#endif
 #ifndef GR_FLOW_CORE
 #define GR_FLOW_CORE 1024  // positions coloured by the single workgroup
 #endif
@@ -484,6 +493,7 @@ __global__ void __launch_bounds__(kCoreThreads) k_jp_core(const int32_t* __restr
                                                           int32_t* abort_flag,
                                                           unsigned spin_limit) {
     __shared__ int32_t lc[GR_FLOW_CORE];
+    __shared__ uint32_t masks[kCoreWaves][kMaskWords];
     const bool hubs = (int64_t)*maxdeg * n > (int64_t)kCoreHubRatio * nnz;
     const int32_t kc = hubs ? (int32_t)(n < GR_FLOW_CORE ? n : GR_FLOW_CORE) : 0;
     if (threadIdx.x == 0) *first_batch = kc == 0 ? 0 : (kc < n ? boff[kc / kFlowBatch] : *nbatches);
@@ -491,9 +501,10 @@ __global__ void __launch_bounds__(kCoreThreads) k_jp_core(const int32_t* __restr
     for (int32_t i = threadIdx.x; i < kc; i += kCoreThreads) lc[i] = -1;
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
+    uint32_t* mask = masks[threadIdx.x / kWave];
     for (int32_t i = threadIdx.x / kWave; i < kc; i += kCoreWaves) {
         const int32_t s = pstart[i], m = pcnt[i];
-        uint64_t used[4] = {0, 0, 0, 0};
+        mask_clear(mask);
         int stop = 0;
         for (int32_t b = lane; b < m && !stop; b += kWave * kFlowU) {
             int32_t u[kFlowU], c[kFlowU];
@@ -508,7 +519,9 @@ __global__ void __launch_bounds__(kCoreThreads) k_jp_core(const int32_t* __restr
             for (int k = 0; k < kFlowU; ++k) {
                 unsigned spins = 0;
                 while (c[k] == -1 && !stop) {
-                    __builtin_amdgcn_s_sleep(1);
+#if GR_CORE_SLEEP
+                    __builtin_amdgcn_s_sleep(GR_CORE_SLEEP);
+#endif
                     c[k] = ld_lds(lc + u[k]);
                     ++spins;
                     if (spins >= spin_limit) {
@@ -520,22 +533,15 @@ __global__ void __launch_bounds__(kCoreThreads) k_jp_core(const int32_t* __restr
                 }
             }
 #pragma unroll
-            for (int k = 0; k < kFlowU; ++k)
-                if (c[k] >= 0 && c[k] < 256) used[c[k] >> 6] |= 1ull << (c[k] & 63);
+            for (int k = 0; k < kFlowU; ++k) mask_set(mask, c[k]);
         }
         if (__ballot(stop)) return;  // the other waves leave at their next check
-#pragma unroll
-        for (int w = 0; w < 4; ++w) used[w] = wave_or(used[w]);
-        int32_t c = first_free4(used, 0);
+        int32_t c = mask_first_free(mask);
         for (int32_t base = 256; c < 0; base += 256) {  // every listed colour is known
-            uint64_t wu[4] = {0, 0, 0, 0};
-            for (int32_t e = lane; e < m; e += kWave) {
-                const int32_t cj = ld_lds(lc + uplist[s + e]);
-                if (cj >= base && cj < base + 256) wu[(cj - base) >> 6] |= 1ull << ((cj - base) & 63);
-            }
-#pragma unroll
-            for (int w = 0; w < 4; ++w) wu[w] = wave_or(wu[w]);
-            c = first_free4(wu, base);
+            mask_clear(mask);
+            for (int32_t e = lane; e < m; e += kWave) mask_set(mask, ld_lds(lc + uplist[s + e]) - base);
+            c = mask_first_free(mask);
+            if (c >= 0) c += base;
         }
         if (lane == 0) {
             __hip_atomic_store(lc + i, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -553,6 +559,7 @@ __global__ void __launch_bounds__(kFlowThreads) k_jp_flow(const int32_t* __restr
                                                           int64_t n, int32_t* cpos,
                                                           int32_t* abort_flag,
                                                           unsigned spin_limit) {
+    __shared__ uint32_t masks[kFlowWaves][kMaskWords];
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t nw = (int64_t)gridDim.x * kFlowWaves;
     const int32_t nbt = *nbatches;
@@ -567,7 +574,9 @@ __global__ void __launch_bounds__(kFlowThreads) k_jp_flow(const int32_t* __restr
             if (!flow_narrow(uplist, s, m, ig, valid, cpos, abort_flag, spin_limit)) return;
         } else {
             const int64_t i = code;
-            if (!flow_wide(uplist, pstart[i], pcnt[i], i, cpos, abort_flag, spin_limit)) return;
+            if (!flow_wide(uplist, pstart[i], pcnt[i], i, cpos, abort_flag, spin_limit,
+                           masks[threadIdx.x / kWave]))
+                return;
         }
     }
 }
