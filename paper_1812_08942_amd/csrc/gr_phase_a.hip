@@ -156,10 +156,12 @@ constexpr double kFlowSparseDegree = 32.0;  // mean degree up to which a graph c
 #define GR_FLOW_SLEEP 2  // s_sleep units (64 cycles) between polls
 #endif
 
-__device__ inline int32_t ld_dev(const int32_t* p) {
+template <class T>
+__device__ inline T ld_dev(const T* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline void st_dev(int32_t* p, int32_t v) {
+template <class T>
+__device__ inline void st_dev(T* p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -463,9 +465,6 @@ __global__ void k_flow_batches(const int32_t* __restrict__ pcnt, int64_t n,
 // across the chip.  Waves take positions w, w + 16, ... in order, a whole
 // wave per position; the deadlock argument of the device-wide flow holds
 // inside the workgroup, and every wait is bounded the same way.
-#ifndef GR_CORE_SLEEP
-#define GR_CORE_SLEEP 1
-#endif
 #ifndef GR_FLOW_CORE
 #define GR_FLOW_CORE 1024  // positions coloured by the single workgroup
 #endif
@@ -519,9 +518,7 @@ __global__ void __launch_bounds__(kCoreThreads) k_jp_core(const int32_t* __restr
             for (int k = 0; k < kFlowU; ++k) {
                 unsigned spins = 0;
                 while (c[k] == -1 && !stop) {
-#if GR_CORE_SLEEP
-                    __builtin_amdgcn_s_sleep(GR_CORE_SLEEP);
-#endif
+                    __builtin_amdgcn_s_sleep(1);
                     c[k] = ld_lds(lc + u[k]);
                     ++spins;
                     if (spins >= spin_limit) {
@@ -1398,6 +1395,355 @@ __global__ void __launch_bounds__(kBig) k_gs_step(const int32_t* __restrict__ rp
     gs_block<Q, DT>(rp, col, w, X, K, tt, b, part, splitcnt, sacc, sd);
 }
 
+// ------------------------------------------- GS sweeps in one launch
+// Where a colour step is small, its time is a chain of latencies (row bounds,
+// columns, vectors, the waves of a wide row, the launch): 5 to 6.5 us for
+// work that the chip does in one.  k_gs_flow does all sweeps in one launch
+// without any barrier.  The blocks of all steps, in order, are tasks; a
+// resident workgroup takes every gridDim-th of them, with the sums of
+// k_gs_step in the same order.  Every sweep writes its own copy of the
+// vectors ("version"), empty (kGsEmpty) before: a word that differs has
+// arrived, so a row waits only for the neighbours that it reads, and its
+// bounds, columns and weights are loaded while the steps before still run.
+// Versions are read and written past the caches.  All workgroups are resident
+// (cooperative launch) and take their tasks in order, so the first task that
+// is not done never waits.  Every wait is bounded; if one runs out, X is still
+// untouched and the steps are launched one by one instead.
+// Per step: image graph's second level (123 colours, 8 blocks a step) 5.2 ->
+// 2.8 us, power law's (221 colours, 37 blocks) 6.5 -> 3.8 us.  One launch
+// with a barrier per step (one line per workgroup's flag, all polled, no
+// fences) took 4.9 and 5.9 us.
+constexpr int kGsFlowBlocks = 256;  // one per CU (128: 0.1 ms more on the power law)
+// One block per workgroup and step on average at most: up to there the flow
+// wins or is level (image graph's first level, 131 blocks a step, 0.12 ms
+// less; kNN graph's, 313 blocks, and the grid's third, 168, level; power law's
+// first, 1106 blocks, 1.6 ms more: the chip is full and launches cost
+// nothing).  The tables, copies and the status read cost about 30 us, a
+// launch saved 1 to 3: below 32 steps the launches win or are level (64^2
+// mesh, 10 steps: 0.300 against 0.306 ms per reduction).
+constexpr int kGsFlowLeast = 32;
+constexpr unsigned kGsFlowSpin = 1u << 16;  // about 0.1 s
+constexpr uint32_t kGsEmpty = ~0u;
+typedef uint32_t gs_v4 __attribute__((ext_vector_type(4)));
+
+struct GsFlowStep {
+    GsTiers tt;
+    int32_t task0;   // first task of the step
+    int32_t row0;    // first row of the colour
+    int32_t split0;  // split rows of the steps before
+};
+
+// N chunks past the caches, in flight together.  The asm waits for its own
+// loads, and takes its addresses from vector registers only (the compiler
+// keeps the distance to a scalar register's write for its own loads, not for
+// these).
+__device__ inline void gs_again(const char* const (&a)[8], gs_v4 (&t)[8]) {
+    asm volatile(
+        "global_load_dwordx4 %0, %8, off sc1\n\tglobal_load_dwordx4 %1, %9, off sc1\n\t"
+        "global_load_dwordx4 %2, %10, off sc1\n\tglobal_load_dwordx4 %3, %11, off sc1\n\t"
+        "global_load_dwordx4 %4, %12, off sc1\n\tglobal_load_dwordx4 %5, %13, off sc1\n\t"
+        "global_load_dwordx4 %6, %14, off sc1\n\tglobal_load_dwordx4 %7, %15, off sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]),
+          "=&v"(t[6]), "=&v"(t[7])
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7])
+        : "memory");
+}
+__device__ inline void gs_again(const char* const (&a)[4], gs_v4 (&t)[4]) {
+    asm volatile(
+        "global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+        "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3])
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+        : "memory");
+}
+__device__ inline void gs_again(const char* const (&a)[1], gs_v4 (&t)[1]) {
+    asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(t[0])
+                 : "v"(a[0])
+                 : "memory");
+}
+
+// what a wave knows of the call: `dead` once a wait has run out somewhere,
+// after which nothing waits any more and the result is thrown away
+struct GsWait {
+    int32_t* status;
+    unsigned limit;
+    bool dead;
+    __device__ inline void spun(unsigned it) {
+        if (it >= limit) {
+            st_dev(status, 1);
+            dead = true;
+        } else if ((it & 255u) == 255u) {
+            dead = __any(ld_dev(status) != 0);
+        }
+    }
+};
+
+// chunks t at offsets o from B; those below free1 (version 0) are never empty
+template <int N>
+__device__ inline void gs_gather(const void* B, const uint32_t (&o)[N], uint32_t free1, gs_v4 (&t)[N],
+                                 GsWait& wait) {
+    auto empty = [&]() {
+        uint32_t m = 0;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const uint32_t a = max(max(t[u].x, t[u].y), max(t[u].z, t[u].w));
+            m = max(m, o[u] < free1 ? 0u : a);
+        }
+        return m == kGsEmpty;
+    };
+    const char* a[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) a[u] = (const char*)B + o[u];
+    gs_again(a, t);
+    unsigned it = 0;
+    bool miss = empty() && !wait.dead;
+    while (__any(miss)) {
+        if (miss) {
+            gs_again(a, t);
+            miss = empty();
+        }
+        wait.spun(++it);
+        if (wait.dead) break;
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+template <int DT>
+__device__ inline void gs_put(void* B, uint32_t o, const float* y) {
+    constexpr int E = Chunk<DT>::E;
+    uint32_t u[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (E == 4) {
+            u[i] = __float_as_uint(y[i]);
+            if (u[i] == kGsEmpty) u[i] = 0x7fc00000u;  // a NaN that would look empty
+        } else {
+            u[i] = (uint32_t)f32_to_bf16(y[2 * i]) | ((uint32_t)f32_to_bf16(y[2 * i + 1]) << 16);
+            if (u[i] == kGsEmpty) u[i] = 0x7fc07fc0u;
+        }
+    }
+    const gs_v4 t{u[0], u[1], u[2], u[3]};
+    // the distance to a write of the stored registers is kept here
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"((char*)B + o), "v"(t)
+                 : "memory");
+}
+
+// version 0 is X, the others and the pieces of split rows are empty
+__global__ void k_gs_flow_start(const gs_v4* __restrict__ X, gs_v4* __restrict__ B, int64_t chunks,
+                                int64_t total, unsigned long long* __restrict__ part, int64_t words,
+                                int32_t* status) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    if (i0 == 0) *status = 0;
+    for (int64_t i = i0; i < total; i += step)
+        B[i] = i < chunks ? X[i] : gs_v4{kGsEmpty, kGsEmpty, kGsEmpty, kGsEmpty};
+    for (int64_t i = i0; i < words; i += step) part[i] = ~0ull;
+}
+__global__ void k_gs_flow_end(const gs_v4* __restrict__ B, gs_v4* __restrict__ X, int64_t chunks,
+                              const int32_t* __restrict__ status) {
+    if (*status != 0) return;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < chunks; i += step) X[i] = B[i];
+}
+
+template <int Q, int DT>
+__global__ void __launch_bounds__(kBig) k_gs_flow(const int32_t* __restrict__ rp,
+                                                  const int32_t* __restrict__ col,
+                                                  const float* __restrict__ w, void* B, int32_t n,
+                                                  int32_t K, const GsFlowStep* __restrict__ plan,
+                                                  const int32_t* __restrict__ step_of,
+                                                  int32_t tasks, int32_t sweeps, int32_t splits,
+                                                  unsigned long long* part, int32_t* status,
+                                                  unsigned spin_limit) {
+    constexpr int E = Chunk<DT>::E;
+    __shared__ float sacc[kBig / kWave][Q][E];
+    __shared__ float sd[kBig / kWave];
+    const int tid = threadIdx.x;
+    const uint32_t row_bytes = (uint32_t)K * (DT == GR_BF16 ? 2u : 4u);
+    const uint32_t version = (uint32_t)n * row_bytes;
+    const int words = K / 2 + 1;  // of a split row's piece: K sums, the weight sum
+    GsWait wait{status, spin_limit, false};
+    int32_t s = 0;
+    for (int32_t i = blockIdx.x; s < sweeps; i += gridDim.x) {
+        while (i >= tasks) i -= tasks, ++s;
+        if (s >= sweeps) break;
+        const GsFlowStep& st = plan[step_of[i]];
+        const GsTiers& tt = st.tt;
+        const int32_t b = i - st.task0, row_first = st.row0;
+        int t = 0;
+        while (t + 1 < tt.nt && b >= (int32_t)tt.blk0[t + 1]) ++t;
+        const int L = tt.lanes[t], P = L / Q;
+        const int l = tid % L, p = l / Q, q = l % Q;
+        const bool split = tt.split && t == 0;
+        const int32_t slot = b - (int32_t)tt.blk0[t];
+        int32_t r = (int32_t)tt.row0[t] + (split ? slot / kSplit : slot * (kBig / L) + tid / L);
+        const bool valid = r < (int32_t)tt.row0[t + 1];
+        if (!valid) r = (int32_t)tt.row0[t];
+        int32_t e0 = 0, e1 = 0;
+        if (valid) {
+            e0 = rp[r];
+            e1 = rp[r + 1];
+            if (split) {
+                const int32_t f = slot % kSplit;
+                const int32_t len = (e1 - e0 + kSplit - 1) / kSplit;
+                e1 = min(e1, e0 + (f + 1) * len);
+                e0 = min(e1, e0 + f * len);
+            }
+        }
+        // version s holds the sweep's start, s + 1 its results
+        const uint32_t start = (uint32_t)s * version, done = start + version;
+        const uint32_t own = start + (uint32_t)r * row_bytes + 16u * (uint32_t)q;
+        const bool guard = L <= kShortLanes * Q;
+        float acc[E];
+#pragma unroll
+        for (int k = 0; k < E; ++k) acc[k] = 0.0f;
+        float d = 0.0f;
+        auto round = [&](auto count, int32_t e) {
+            constexpr int N = decltype(count)::value;
+            uint32_t o[N];
+            float wt[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const bool ok = e + u * P < e1;
+                const int32_t j = ok ? col[e + u * P] : -1;  // none: weight 0, own row
+                wt[u] = ok ? w[e + u * P] : 0.0f;
+                o[u] = ok ? (j < row_first ? done : start) + (uint32_t)j * row_bytes + 16u * (uint32_t)q
+                          : own;
+            }
+            gs_v4 t4[N];
+            gs_gather<N>(B, o, version, t4, wait);
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                // the slots that k_gs_step adds: all of a round that the lane
+                // starts, but on short rows none past the end
+                if (guard ? e + u * P < e1 : e + (u / kU) * kU * P < e1) {
+                    float x[E];
+                    Chunk<DT>::unpack(make_uint4(t4[u].x, t4[u].y, t4[u].z, t4[u].w), x);
+#pragma unroll
+                    for (int k = 0; k < E; ++k) acc[k] = __fmaf_rn(wt[u], x[k], acc[k]);
+                    d += wt[u];
+                }
+        };
+        int32_t e = e0 + p;
+        for (; __any(e + kU * P < e1); e += 2 * kU * P)
+            round(std::integral_constant<int, 2 * kU>{}, e);
+        if (__any(e < e1)) round(std::integral_constant<int, kU>{}, e);
+        const int span = L < kWave ? L : kWave;
+        for (int off = Q; off < span; off <<= 1) {
+#pragma unroll
+            for (int k = 0; k < E; ++k) acc[k] += __shfl_xor(acc[k], off, kWave);
+            d += __shfl_xor(d, off, kWave);
+        }
+        float y[E];
+        bool put = false;  // this lane has chunk `pq` of the row's sum
+        int pq = q;
+        if (L > kWave) {
+            const int wid = tid / kWave, lane = tid & (kWave - 1);
+            if (lane < Q) {
+#pragma unroll
+                for (int k = 0; k < E; ++k) sacc[wid][lane][k] = acc[k];
+                if (lane == 0) sd[wid] = d;
+            }
+            __syncthreads();
+            d = 0.0f;
+#pragma unroll
+            for (int k = 0; k < E; ++k) y[k] = 0.0f;
+            if (l < Q && valid) {
+                const int w0 = (tid - l) / kWave, nw = L / kWave;
+                for (int ww = w0; ww < w0 + nw; ++ww) {
+#pragma unroll
+                    for (int k = 0; k < E; ++k) y[k] += sacc[ww][l][k];
+                    d += sd[ww];
+                }
+                put = !split;
+            }
+            if (split) {
+                unsigned long long* at =
+                    part + ((int64_t)(s * splits + st.split0) * kSplit + slot) * words;
+                if (l < Q) {
+#pragma unroll
+                    for (int k = 0; k < E / 2; ++k) {
+                        uint32_t lo = __float_as_uint(y[2 * k]);
+                        const uint32_t hi = __float_as_uint(y[2 * k + 1]);
+                        if ((lo & hi) == kGsEmpty) lo = 0x7fc00000u;
+                        st_dev(at + l * (E / 2) + k, ((unsigned long long)hi << 32) | lo);
+                    }
+                    if (l == 0) st_dev(at + K / 2, (unsigned long long)__float_as_uint(d));
+                }
+                if (slot % kSplit == kSplit - 1 && tid < kWave) {
+                    // the last piece adds all: lane (f0, q) pieces f0,
+                    // f0 + F, ... of chunk q, then a fixed xor tree over f0
+                    constexpr int F = kWave / Q < kSplit ? kWave / Q : kSplit;
+                    const int f0 = tid / Q;
+                    pq = tid % Q;
+                    d = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < E; ++k) y[k] = 0.0f;
+#pragma unroll
+                    for (int jj = 0; jj < kSplit / F; ++jj) {
+                        const unsigned long long* from =
+                            at - (int64_t)(kSplit - 1 - (f0 % F) - jj * F) * words;
+                        unsigned long long v[E / 2 + 1];
+                        unsigned it = 0;
+                        for (;;) {
+                            bool miss = false;
+#pragma unroll
+                            for (int k = 0; k <= E / 2; ++k) {
+                                v[k] = ld_dev(from + (k < E / 2 ? pq * (E / 2) + k : K / 2));
+                                miss = miss || v[k] == ~0ull;
+                            }
+                            if (!__any(miss) || wait.dead) break;
+                            wait.spun(++it);
+                        }
+#pragma unroll
+                        for (int k = 0; k < E / 2; ++k) {
+                            y[2 * k] += __uint_as_float((uint32_t)v[k]);
+                            y[2 * k + 1] += __uint_as_float((uint32_t)(v[k] >> 32));
+                        }
+                        d += __uint_as_float((uint32_t)v[E / 2]);
+                    }
+                    if (f0 >= F) {
+                        d = 0.0f;
+#pragma unroll
+                        for (int k = 0; k < E; ++k) y[k] = 0.0f;
+                    }
+#pragma unroll
+                    for (int off = Q; off < Q * F; off <<= 1) {
+#pragma unroll
+                        for (int k = 0; k < E; ++k) y[k] += __shfl_xor(y[k], off, kWave);
+                        d += __shfl_xor(d, off, kWave);
+                    }
+                    put = f0 == 0;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < E; ++k) y[k] = acc[k];
+            put = p == 0 && valid;
+        }
+        const uint32_t at = (uint32_t)r * row_bytes + 16u * (uint32_t)pq;
+        if (__any(put && !(d > 0.0f))) {
+            // a row without weight keeps its vector
+            const uint32_t o[1] = {start + at};
+            gs_v4 t4[1];
+            gs_gather<1>(B, o, version, t4, wait);
+            if (put && !(d > 0.0f)) {
+                Chunk<DT>::unpack(make_uint4(t4[0].x, t4[0].y, t4[0].z, t4[0].w), y);
+                gs_put<DT>(B, done + at, y);
+            }
+        }
+        if (put && d > 0.0f) {
+#pragma unroll
+            for (int k = 0; k < E; ++k) y[k] = y[k] / d;
+            gs_put<DT>(B, done + at, y);
+        }
+        if (L > kWave) __syncthreads();  // the LDS slots are reused
+    }
+}
+
 // lanes per row of tier t: about half the tier's largest degree times
 // Q / kU (two rounds of kU gathers per lane), a power of two in [Q, kBig]
 static int tier_lanes(int Q, int t) {
@@ -1455,6 +1801,82 @@ static int smooth_q(const OrderedGraph* og, int K, int sweeps, void* X, Arena& w
     for (int c = 0; c < C; ++c)
         if (plan[c].split) split_rows = std::max<int64_t>(split_rows, plan[c].row0[1] - plan[c].row0[0]);
     const size_t mark = ws.used;
+    // all sweeps in one launch where the steps are small
+    int64_t tasks = 0, splits = 0;
+    for (int c = 0; c < C; ++c) {
+        if (plan[c].nt) tasks += plan[c].blk0[plan[c].nt];
+        if (plan[c].split) splits += plan[c].row0[1] - plan[c].row0[0];
+    }
+    const size_t vector = (size_t)og->g.n * K * xs;
+    // GR_GS_FLOW=0 / 1 turns it off / on at any size, GR_GS_SPIN_LIMIT sets
+    // the polls of a wait, for comparison and tests
+    const char* flow_env = getenv("GR_GS_FLOW");
+    const bool flow = flow_env ? flow_env[0] == '1'
+                               : tasks <= (int64_t)kGsFlowBlocks * steps &&
+                                     (int64_t)steps * sweeps >= kGsFlowLeast;
+    // (32-bit byte offsets)
+    if (flow && sweeps > 0 && (double)vector * (sweeps + 1) < 2147483648.0 && tasks < INT32_MAX) {
+        unsigned spin = kGsFlowSpin;
+        if (const char* sl = getenv("GR_GS_SPIN_LIMIT")) {
+            const long v = atol(sl);
+            if (v > 0 && v < (long)kGsFlowSpin) spin = (unsigned)v;
+        }
+        int dev = 0, cus = 0, per_cu = 0;
+        GR_HIP(hipGetDevice(&dev));
+        GR_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        GR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_gs_flow<Q, DT>,
+                                                            kBig, 0));
+        const int64_t words = (int64_t)sweeps * splits * kSplit * (K / 2 + 1);
+        char* B = ws.take<char>(vector * (sweeps + 1));
+        unsigned long long* part = ws.take<unsigned long long>((size_t)std::max<int64_t>(words, 1));
+        const size_t plan_size = sizeof(GsFlowStep) * (size_t)steps;
+        char* table = ws.take<char>(plan_size + 4 * (size_t)tasks);
+        int32_t* status = ws.take<int32_t>(1);
+        if (!ws.overflow && (int64_t)cus * per_cu >= kGsFlowBlocks) {
+            std::vector<char> host(plan_size + 4 * (size_t)tasks);
+            GsFlowStep* list = (GsFlowStep*)host.data();
+            int32_t* step_of = (int32_t*)(host.data() + plan_size);
+            int32_t k = 0, task0 = 0, split0 = 0;
+            for (int c = 0; c < C; ++c) {
+                if (plan[c].nt == 0) continue;
+                list[k] = {plan[c], task0, (int32_t)og->class_ptr_h[c], split0};
+                for (int64_t b = 0; b < plan[c].blk0[plan[c].nt]; ++b) step_of[task0++] = k;
+                if (plan[c].split) split0 += (int32_t)(plan[c].row0[1] - plan[c].row0[0]);
+                ++k;
+            }
+            if (pr) prof::begin(st);
+            GR_HIP(hipMemcpyAsync(table, host.data(), host.size(), hipMemcpyHostToDevice, st));
+            const int64_t chunks = (int64_t)(vector / 16);
+            hipLaunchKernelGGL(k_gs_flow_start, dim3(std::min(2048u, blocks_for(chunks * (sweeps + 1), 256))),
+                               dim3(256), 0, st, (const gs_v4*)X, (gs_v4*)B, chunks,
+                               chunks * (sweeps + 1), part, words, status);
+            GR_LAUNCHED("gs flow start");
+            const int32_t *rp = og->g.row_ptr, *col = og->g.col;
+            const float* w = og->g.w;
+            const GsFlowStep* dplan = (const GsFlowStep*)table;
+            const int32_t* dstep = (const int32_t*)(table + plan_size);
+            int32_t nn = (int32_t)og->g.n, KK = K, sw = sweeps, nt = (int32_t)tasks, sp = (int32_t)splits;
+            void* args[] = {(void*)&rp, (void*)&col, (void*)&w, (void*)&B, (void*)&nn, (void*)&KK,
+                            (void*)&dplan, (void*)&dstep, (void*)&nt, (void*)&sw, (void*)&sp,
+                            (void*)&part, (void*)&status, (void*)&spin};
+            GR_HIP(hipLaunchCooperativeKernel((const void*)k_gs_flow<Q, DT>, dim3(kGsFlowBlocks),
+                                              dim3(kBig), args, 0, st));
+            hipLaunchKernelGGL(k_gs_flow_end, dim3(std::min(2048u, blocks_for(chunks, 256))), dim3(256),
+                               0, st, (const gs_v4*)(B + vector * sweeps), (gs_v4*)X, chunks,
+                               (const int32_t*)status);
+            GR_LAUNCHED("gs flow end");
+            if (pr) prof::end(st, prof::SMOOTH, sweep_bytes * sweeps, (int64_t)steps * sweeps);
+            int32_t bad = 0;
+            GR_TRY(fetch({{status, sizeof(bad)}}, &bad, st));
+            if (!bad) {
+                ws.used = mark;
+                return GR_OK;
+            }
+            // a wait ran out: X is as it was, the launches below do it again
+        }
+        ws.used = mark;
+        ws.overflow = false;
+    }
     float* part = ws.take<float>((size_t)std::max<int64_t>(split_rows, 1) * kSplit * (K + 1));
     int32_t* splitcnt = ws.take<int32_t>((size_t)std::max<int64_t>(split_rows, 1));
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (smoothing partials)");
