@@ -100,23 +100,36 @@ __global__ void k_jump(int32_t* __restrict__ pa, int64_t n, int32_t* __restrict_
     if (changed && __ballot(ch) && (threadIdx.x & (kWave - 1)) == 0) *changed = 1;
 }
 
+// Smallest id of every aggregate.  A row reads the smallest id so far first
+// and skips the atomic if its own is larger: same-address atomics serialise,
+// and a hub's aggregate has a tenth of all rows.  A stale read only costs an
+// atomic that changes nothing, but with a row per thread every read of a
+// small graph came before the first atomic (power law: 286 us).  So a thread
+// takes kMinRows rows in turn, and reads past the caches.
+constexpr int kMinRows = 8;
 __global__ void k_min_member(const int32_t* __restrict__ root, const int32_t* __restrict__ ids,
-                             int64_t n, int32_t* __restrict__ minid) {
-    int64_t v = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (!ids) {
-        // ids are the rows: of a run of lanes with one root (members next to
-        // each other) the first has the smallest id; the others stay out of
-        // the atomics on that address
-        const int32_t r = v < n ? root[v] : -1;
-        const int32_t rp = __shfl_up(r, 1, kWave);
-        if ((threadIdx.x & (kWave - 1)) > 0 && rp == r) return;
+                             int64_t n, int32_t* minid) {
+    const int64_t step = (int64_t)gridDim.x * kT;
+    const int64_t v0 = (int64_t)blockIdx.x * kT + threadIdx.x;
+    int32_t r[kMinRows], id[kMinRows];
+#pragma unroll
+    for (int u = 0; u < kMinRows; ++u) {
+        const int64_t v = v0 + u * step;
+        r[u] = v < n ? root[v] : -1;
+        id[u] = v < n ? idof(ids, (int32_t)v) : 0;
     }
-    if (v >= n) return;
-    // read first: once a small id has arrived, the larger ones of a big
-    // aggregate skip the atomic (same-address atomics serialise); a stale
-    // read only costs an atomic that changes nothing
-    const int32_t r = root[v], id = idof(ids, (int32_t)v);
-    if (id < minid[r]) atomicMin(&minid[r], id);
+#pragma unroll
+    for (int u = 0; u < kMinRows; ++u) {
+        bool go = r[u] >= 0;
+        if (!ids) {
+            // ids are the rows: of a run of lanes with one root (members
+            // next to each other) the first has the smallest id
+            const int32_t rp = __shfl_up(r[u], 1, kWave);
+            go = go && !((threadIdx.x & (kWave - 1)) > 0 && rp == r[u]);
+        }
+        if (go && id[u] < __hip_atomic_load(minid + r[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMin(&minid[r[u]], id[u]);
+    }
 }
 
 __global__ void k_leader_flags(const int32_t* __restrict__ root, const int32_t* __restrict__ ids,
@@ -547,23 +560,25 @@ __global__ void __launch_bounds__(kT) k_seg_sort_lds(const int32_t* __restrict__
         sv[i] = i < c ? ew[o + i] : 0.0f;
     }
     __syncthreads();
+    // a thread per pair; up to j = 64 the pairs of a wave's 64 threads are 128
+    // entries that no other wave touches, and no barrier is needed
     for (int k = 2; k <= P; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = tid; i < P; i += kT) {
-                const int p = i ^ j;
-                if (p > i) {
-                    const bool up = (i & k) == 0;
-                    const uint64_t a = sk[i], b = sk[p];
-                    if ((a > b) == up) {
-                        sk[i] = b;
-                        sk[p] = a;
-                        const float t = sv[i];
-                        sv[i] = sv[p];
-                        sv[p] = t;
-                    }
+            for (int t = tid; t < P / 2; t += kT) {
+                const int i = 2 * t - (t & (j - 1)), p = i + j;
+                const bool up = (i & k) == 0;
+                const uint64_t a = sk[i], b = sk[p];
+                if ((a > b) == up) {
+                    sk[i] = b;
+                    sk[p] = a;
+                    const float x = sv[i];
+                    sv[i] = sv[p];
+                    sv[p] = x;
                 }
             }
-            __syncthreads();
+            const int next = j > 1 ? j >> 1 : k;  // the next stage's j
+            if (j > kWave || next > kWave || (j == 1 && k == P)) __syncthreads();
+            else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
     // runs: heads counted in chunk order, each head sums its run
