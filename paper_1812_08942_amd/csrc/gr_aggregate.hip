@@ -229,7 +229,7 @@ int aggregate(const gr_graph* g, const int32_t* best, const float* dbest, const 
                                b == kJumpBatch - 1 ? small : (int32_t*)nullptr);
             GR_LAUNCHED("jump");
         }
-        hipLaunchKernelGGL(k_min_member, dim3(gb), dim3(kT), 0, st, root, ids, n, minid);
+        hipLaunchKernelGGL(k_min_member, dim3(blocks_for(n, kT * kMinRows)), dim3(kT), 0, st, root, ids, n, minid);
         GR_LAUNCHED("min member");
         hipLaunchKernelGGL(k_leader_flags, dim3(gb), dim3(kT), 0, st, root, ids, minid, n, flag_by_id);
         GR_LAUNCHED("leader flags");
