@@ -391,10 +391,12 @@ __device__ inline void res_load(const unsigned long long* z, int32_t m, res_v4* 
 #pragma unroll
     for (int u = 0; u < kResF; ++u)
         o[u] = 16u * (unsigned)min((int)threadIdx.x + u * kResThreads, m / 2 - 1);
-    // waits for its own loads: none is in flight past the block
+    // waits for its own loads: none is in flight past the block; and starts
+    // with the distance that a load keeps to a vector instruction that wrote
+    // its scalar address (the compiler keeps it for its own loads only)
     if (m <= kResN / 2) {
         asm volatile(
-            "global_load_dwordx4 %0, %4, %8 sc1\n\tglobal_load_dwordx4 %1, %5, %8 sc1\n\t"
+            "s_nop 4\n\tglobal_load_dwordx4 %0, %4, %8 sc1\n\tglobal_load_dwordx4 %1, %5, %8 sc1\n\t"
             "global_load_dwordx4 %2, %6, %8 sc1\n\tglobal_load_dwordx4 %3, %7, %8 sc1\n\t"
             "s_waitcnt vmcnt(0)"
             : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3])
@@ -403,7 +405,7 @@ __device__ inline void res_load(const unsigned long long* z, int32_t m, res_v4* 
         t[4] = t[5] = t[6] = t[7] = t[0];
     } else {
         asm volatile(
-            "global_load_dwordx4 %0, %8, %16 sc1\n\tglobal_load_dwordx4 %1, %9, %16 sc1\n\t"
+            "s_nop 4\n\tglobal_load_dwordx4 %0, %8, %16 sc1\n\tglobal_load_dwordx4 %1, %9, %16 sc1\n\t"
             "global_load_dwordx4 %2, %10, %16 sc1\n\tglobal_load_dwordx4 %3, %11, %16 sc1\n\t"
             "global_load_dwordx4 %4, %12, %16 sc1\n\tglobal_load_dwordx4 %5, %13, %16 sc1\n\t"
             "global_load_dwordx4 %6, %14, %16 sc1\n\tglobal_load_dwordx4 %7, %15, %16 sc1\n\t"
