@@ -143,8 +143,9 @@ constexpr int kFlowBatch = kWave / kFlowG;     // positions of a batch
 constexpr int32_t kFlowNarrow = 64;            // listed neighbours per position of a narrow batch
 // resident workgroups per CU of the flow: more waves take more batches at
 // once where the dependence chains are short (sparse graphs: grid colour
-// phase 3.5 -> 3.07 ms with 8), fewer where long chains keep most waves
-// polling (power law: 3.16 ms with 2, 3.66 with 8)
+// phase 3.71, 2.91, 2.54 and 2.51 ms with 1, 2, 4 and 8; kNN graph 0.55,
+// 0.54, 0.53, 0.54), fewer where long chains keep most waves polling (power
+// law: 2.34 ms with 1, 2.35 with 2, 2.50 with 4)
 #ifndef GR_FLOW_BLOCKS_PER_CU
 #define GR_FLOW_BLOCKS_PER_CU 2
 #endif
