@@ -232,7 +232,7 @@ def run_workload(G, key, dtype, steps, warmup, g=None):
         "profiled_ms_per_step": ms_prof,
         "roofline": {
             "bound": "hbm",
-            "kernel": "Gauss-Seidel colour step (k_gs_step)",
+            "kernel": "Gauss-Seidel colour step (k_gs_step, k_gs_flow)",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
