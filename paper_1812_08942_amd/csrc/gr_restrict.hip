@@ -12,10 +12,11 @@ namespace gr {
 
 constexpr int kRT = 256;
 constexpr int kRPiece = 256;  // members per piece
+constexpr int kRRows = 8;     // rows in flight per thread
 
 // flag bits: 1 = an aggregate id outside [0, n_coarse), 2 = an empty aggregate
 __global__ void k_restrict_keys(const int32_t* __restrict__ agg, int64_t n, int64_t nc,
-                                uint64_t* __restrict__ key, uint32_t* __restrict__ val,
+                                uint32_t* __restrict__ key, uint32_t* __restrict__ val,
                                 int32_t* bad) {
     const int64_t v = (int64_t)blockIdx.x * kRT + threadIdx.x;
     if (v >= n) return;
@@ -24,12 +25,12 @@ __global__ void k_restrict_keys(const int32_t* __restrict__ agg, int64_t n, int6
         atomicOr(bad, 1);
         a = 0;
     }
-    key[v] = (uint64_t)a;
+    key[v] = (uint32_t)a;
     val[v] = (uint32_t)v;
 }
 
 // mstart[c] = the first sorted position whose aggregate is >= c; k over [0, n]
-__global__ void k_member_bounds(const uint64_t* __restrict__ skey, int64_t n, int64_t nc,
+__global__ void k_member_bounds(const uint32_t* __restrict__ skey, int64_t n, int64_t nc,
                                 int32_t* __restrict__ mstart) {
     const int64_t k = (int64_t)blockIdx.x * kRT + threadIdx.x;
     if (k > n) return;
@@ -54,42 +55,80 @@ __global__ void k_restrict_piece_rows(const int32_t* __restrict__ ppos, int64_t 
     for (int32_t k = ppos[c]; k < ppos[c + 1]; ++k) prow[k] = (int32_t)c;
 }
 
-// a thread per (piece, column): the FP64 sum of the piece's members in order
-template <class T>
+// V neighbouring columns of a row
+template <int V, class T>
+struct alignas(V * sizeof(T)) RCols {
+    T x[V];
+};
+
+// A thread per (piece, V columns): the FP64 sums of the piece's members in
+// order.  Bound by one read of F.  An aggregate of one piece is finished here
+// (FR: the mean), so that only the others pass through `part`: writing every
+// piece's sums and reading them back took a second launch and, at 70,000 x
+// 784 and 4,375 aggregates, 55 of 290 MB (52 + 13 -> 43 + 5 us, 5.4 TB/s).
+// V = 2 where d and the arrays allow 8-byte loads, kRRows rows in flight: 4
+// or 8 rows take 50 or 46 us at V = 1, 55 or 43 at V = 2, 66 or 46 at V = 4
+// (wider loads leave fewer threads to hide the members' latency).
+template <int V, class T>
 __global__ void k_restrict_pieces(const uint32_t* __restrict__ members,
                                   const int32_t* __restrict__ mstart,
                                   const int32_t* __restrict__ ppos,
                                   const int32_t* __restrict__ prow, int64_t npieces, int32_t d,
-                                  const T* __restrict__ F, double* __restrict__ part) {
+                                  const T* __restrict__ F, double* __restrict__ part,
+                                  float* __restrict__ FR) {
     const int64_t t = (int64_t)blockIdx.x * kRT + threadIdx.x;
-    const int64_t k = t / d;
-    const int32_t col = (int32_t)(t % d);
+    const int32_t dv = d / V;
+    int64_t k;
+    if (npieces * dv <= 0xffffffffll) k = (int64_t)((uint32_t)t / (uint32_t)dv);
+    else k = t / dv;
     if (k >= npieces) return;
+    const int32_t col = (int32_t)(t - k * dv) * V;
     const int32_t c = prow[k];
-    const int32_t m0 = mstart[c] + (int32_t)(k - ppos[c]) * kRPiece;
-    const int32_t m1 = min(m0 + kRPiece, mstart[c + 1]);
-    double s = 0.0;
+    const int32_t first = mstart[c], end = mstart[c + 1];
+    const int32_t m0 = first + (int32_t)(k - ppos[c]) * kRPiece;
+    const int32_t m1 = min(m0 + kRPiece, end);
+    auto cols = [&](int32_t m) {
+        return *reinterpret_cast<const RCols<V, T>*>(F + (int64_t)members[m] * d + col);
+    };
+    double s[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) s[v] = 0.0;
     int32_t m = m0;
-    for (; m + 4 <= m1; m += 4) {  // four rows in flight, added in member order
-        T x[4];
+    for (; m + kRRows <= m1; m += kRRows) {  // added in member order
+        RCols<V, T> r[kRRows];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = F[(int64_t)members[m + u] * d + col];
+        for (int u = 0; u < kRRows; ++u) r[u] = cols(m + u);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s += (double)x[u];
+        for (int u = 0; u < kRRows; ++u)
+#pragma unroll
+            for (int v = 0; v < V; ++v) s[v] += (double)r[u].x[v];
     }
-    for (; m < m1; ++m) s += (double)F[(int64_t)members[m] * d + col];
-    part[k * d + col] = s;
+    for (; m < m1; ++m) {
+        const RCols<V, T> r = cols(m);
+#pragma unroll
+        for (int v = 0; v < V; ++v) s[v] += (double)r.x[v];
+    }
+    if (FR && end - first <= kRPiece) {
+        RCols<V, float> o;
+#pragma unroll
+        for (int v = 0; v < V; ++v) o.x[v] = (float)(s[v] / (double)(end - first));
+        *reinterpret_cast<RCols<V, float>*>(FR + (int64_t)c * d + col) = o;
+    } else {
+#pragma unroll
+        for (int v = 0; v < V; ++v) part[k * d + col + v] = s[v];
+    }
 }
 
 // a thread per (aggregate, column): its pieces in order, over the member
-// count (the mean, float32) or not (the sum, FP64)
+// count (the mean, float32; aggregates of several pieces only) or not (the
+// sum, FP64)
 __global__ void k_restrict_final(const int32_t* __restrict__ mstart,
                                  const int32_t* __restrict__ ppos, int64_t nc, int32_t d,
                                  const double* __restrict__ part, float* __restrict__ FR) {
     const int64_t t = (int64_t)blockIdx.x * kRT + threadIdx.x;
     const int64_t c = t / d;
     const int32_t col = (int32_t)(t % d);
-    if (c >= nc) return;
+    if (c >= nc || ppos[c + 1] - ppos[c] < 2) return;
     double s = 0.0;
     for (int32_t k = ppos[c]; k < ppos[c + 1]; ++k) s += part[(int64_t)k * d + col];
     FR[c * d + col] = (float)(s / (double)(mstart[c + 1] - mstart[c]));
@@ -122,22 +161,22 @@ template <class T>
 static int restrict_rows(const int32_t* agg, int64_t n, int64_t nc, int32_t d, const T* F,
                          float* FR32, double* FR64, Arena& ws, hipStream_t st) {
     const size_t mark = ws.used;
-    uint64_t* k0 = ws.take<uint64_t>(n);
+    uint32_t* k0 = ws.take<uint32_t>(n);
     uint32_t* v0 = ws.take<uint32_t>(n);
-    uint64_t* k1 = ws.take<uint64_t>(n);
+    uint32_t* k1 = ws.take<uint32_t>(n);
     uint32_t* v1 = ws.take<uint32_t>(n);
     int32_t* mstart = ws.take<int32_t>(nc + 1);
     int32_t* cnt = ws.take<int32_t>(nc);
     int32_t* ppos = ws.take<int32_t>(nc + 1);
     int32_t* bad = ws.take<int32_t>(4);
     if (ws.overflow) return set_error(GR_ENOMEM, "workspace too small (restriction)");
-    GR_HIP(hipMemsetAsync(bad, 0, sizeof(int32_t) * 4, st));
+    GR_TRY(fill_i32(bad, 0, 4, st));
     hipLaunchKernelGGL(k_restrict_keys, dim3(blocks_for(n, kRT)), dim3(kRT), 0, st, agg, n, nc, k0, v0,
                        bad);
     GR_LAUNCHED("restrict keys");
-    GR_TRY(radix_sort_pairs(k0, v0, k1, v1, n, bits_for(nc), ws, st));
+    GR_TRY(radix_sort_pairs32(k0, v0, k1, v1, n, bits_for(nc), ws, st));
     hipLaunchKernelGGL(k_member_bounds, dim3(blocks_for(n + 1, kRT)), dim3(kRT), 0, st,
-                       (const uint64_t*)k1, n, nc, mstart);
+                       (const uint32_t*)k1, n, nc, mstart);
     GR_LAUNCHED("member bounds");
     hipLaunchKernelGGL(k_restrict_piece_counts, dim3(blocks_for(nc, kRT)), dim3(kRT), 0, st,
                        (const int32_t*)mstart, nc, cnt, bad);
@@ -154,14 +193,18 @@ static int restrict_rows(const int32_t* agg, int64_t n, int64_t nc, int32_t d, c
     hipLaunchKernelGGL(k_restrict_piece_rows, dim3(blocks_for(nc, kRT)), dim3(kRT), 0, st,
                        (const int32_t*)ppos, nc, prow);
     GR_LAUNCHED("piece rows");
-    hipLaunchKernelGGL(k_restrict_pieces<T>, dim3(blocks_for(np * d, kRT)), dim3(kRT), 0, st,
-                       (const uint32_t*)v1, (const int32_t*)mstart, (const int32_t*)ppos,
-                       (const int32_t*)prow, np, d, F, part);
+    const bool wide = d % 2 == 0 && (uintptr_t)F % (2 * sizeof(T)) == 0 && (uintptr_t)FR32 % 8 == 0;
+    const int V = wide ? 2 : 1;
+    hipLaunchKernelGGL((wide ? k_restrict_pieces<2, T> : k_restrict_pieces<1, T>),
+                       dim3(blocks_for(np * (d / V), kRT)), dim3(kRT), 0, st, (const uint32_t*)v1,
+                       (const int32_t*)mstart, (const int32_t*)ppos, (const int32_t*)prow, np, d, F, part,
+                       FR32);
     GR_LAUNCHED("restrict pieces");
     if (FR32) {
-        hipLaunchKernelGGL(k_restrict_final, dim3(blocks_for(nc * d, kRT)), dim3(kRT), 0, st,
-                           (const int32_t*)mstart, (const int32_t*)ppos, nc, d, (const double*)part,
-                           FR32);
+        if (np > nc)
+            hipLaunchKernelGGL(k_restrict_final, dim3(blocks_for(nc * d, kRT)), dim3(kRT), 0, st,
+                               (const int32_t*)mstart, (const int32_t*)ppos, nc, d,
+                               (const double*)part, FR32);
     } else {
         hipLaunchKernelGGL(k_restrict_final_sum, dim3(blocks_for(nc * d, kRT)), dim3(kRT), 0, st,
                            (const int32_t*)ppos, nc, d, (const double*)part, FR64);
