@@ -502,12 +502,14 @@ __global__ void __launch_bounds__(256) k_vjp_rows(
     if (r >= hi) return;
     const int32_t e0 = rp[r], e1 = rp[r + 1];
     const float d = dw[r];
-    if (!(d > 0.0f)) {  // no neighbours: no step changes this row
+    if (!(d > 0.0f)) {  // no neighbours, or no weight: no step changes this row
         if (FINAL && p == 0) {
             float gi[E];
             load_f32<E>(G, r, K, q, gi);
             store_f32<E>(out, r, K, q, gi);
         }
+        if (!FINAL && first && q == 0)
+            for (int32_t e = e0 + p; e < e1; e += P) ge[e] = 0.0f;
         return;
     }
     float acc[E];
