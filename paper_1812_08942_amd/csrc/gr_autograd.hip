@@ -894,14 +894,10 @@ struct VjpStates {
             if (holds[i] == s) return (int)i;
         return -1;
     }
-    int copy(int from, int to) {
-        GR_HIP(hipMemcpyAsync(slot[to], slot[from], xbytes, hipMemcpyDeviceToDevice, st));
-        holds[to] = holds[from];
-        return GR_OK;
-    }
-    int sweep(int i, int sweeps) {
-        GR_TRY(smooth_ordered(og, K, sweeps, DT, slot[i], ws, st));
-        holds[i] += sweeps;
+    // `sweeps` sweeps on from slot `from`, into slot `to` (the same one or not)
+    int sweep(int from, int to, int sweeps) {
+        GR_TRY(smooth_ordered(og, K, sweeps, DT, slot[to], ws, st, from == to ? nullptr : slot[from]));
+        holds[to] = holds[from] + sweeps;
         return GR_OK;
     }
     // state s into a slot other than `keep`, from the nearest earlier one
@@ -911,15 +907,14 @@ struct VjpStates {
         for (size_t i = 0; i < slot.size(); ++i)
             if (holds[i] >= 0 && holds[i] < s && holds[i] > holds[from]) from = (int)i;
         const int to = keep == 1 ? 2 : 1;  // of the two slots in use
-        if (from != to) GR_TRY(copy(from, to));
-        for (size_t i = 3; i < slot.size() && holds[to] + 1 < s; ++i) {
+        for (size_t i = 3; i < slot.size() && holds[from] + 1 < s; ++i) {
             const bool free = holds[i] < 0 || holds[i] > s;
             if (!free || (int)i == keep) continue;
             const int left = (int)(slot.size() - i);  // spare slots from here on
-            GR_TRY(sweep(to, (s - holds[to] + left) / (left + 1)));
-            GR_TRY(copy(to, (int)i));
+            GR_TRY(sweep(from, (int)i, (s - holds[from] + left) / (left + 1)));
+            from = (int)i;
         }
-        if (holds[to] < s) GR_TRY(sweep(to, s - holds[to]));
+        GR_TRY(sweep(from, to, s - holds[from]));
         *at = to;
         return GR_OK;
     }
@@ -930,8 +925,7 @@ struct VjpStates {
             GR_TRY(build(s - 1, -1, &p));
             q = p == 1 ? 2 : 1;
             if (store) q = s;
-            GR_TRY(copy(p, q));
-            GR_TRY(sweep(q, 1));
+            GR_TRY(sweep(p, q, 1));
         } else {
             GR_TRY(build(s - 1, q, &p));
         }
@@ -954,10 +948,7 @@ static int vjp_impl(const VjpPlan& pl, int K, int S, int store, void* states, si
     X.holds.assign(X.slot.size(), -1);
     X.holds[0] = 0;
     if (store)
-        for (int s = 1; s <= S; ++s) {
-            GR_TRY(X.copy(s - 1, s));
-            GR_TRY(X.sweep(s, 1));
-        }
+        for (int s = 1; s <= S; ++s) GR_TRY(X.sweep(s - 1, s, 1));
     for (int s = S; s >= 1; --s) {
         const void *Xs, *Xp;
         GR_TRY(X.pair(s, &Xp, &Xs));

@@ -1205,13 +1205,19 @@ struct GsTiers {
     int32_t reverse;            // blocks from blk0[split] on run in reverse order
 };
 
-template <int Q, int DT>
+// FROM: a sweep out of place.  X0 holds the vectors of the sweep's start, X
+// takes every row's new one; rows below `first` (the colour's first row)
+// have theirs, the others are read from X0.  It spares the copy before a
+// sweep whose start is kept (127^3 grid, bf16: 52 us each).
+template <int Q, int DT, bool FROM>
 __device__ inline void gs_block(const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                const float* __restrict__ w, void* __restrict__ X, int32_t K,
-                                const GsTiers& tt, int64_t b, float* __restrict__ part,
+                                const float* __restrict__ w, void* __restrict__ X,
+                                const void* __restrict__ X0, int32_t K, const GsTiers& tt, int64_t b, float* __restrict__ part,
                                 int32_t* __restrict__ splitcnt, float (*sacc)[Q][Chunk<DT>::E],
                                 float* sd) {
     constexpr int E = Chunk<DT>::E;
+    const int32_t first = (int32_t)tt.row0[0];
+    auto at = [&](int32_t j) -> const void* { return FROM && j >= first ? X0 : X; };
     int t = 0;
     while (t + 1 < tt.nt && b >= tt.blk0[t + 1]) ++t;
     const int L = tt.lanes[t];
@@ -1260,7 +1266,7 @@ __device__ inline void gs_block(const int32_t* __restrict__ rp, const int32_t* _
             uint4 raw[kU];
 #pragma unroll
             for (int u = 0; u < kU; ++u)
-                if (u == 0 || __any(e + u * P < e1)) raw[u] = Chunk<DT>::raw(X, j[u], K, q);
+                if (u == 0 || __any(e + u * P < e1)) raw[u] = Chunk<DT>::raw(at(j[u]), j[u], K, q);
 #pragma unroll
             for (int u = 0; u < kU; ++u)
                 if (e + u * P < e1) {
@@ -1284,7 +1290,7 @@ __device__ inline void gs_block(const int32_t* __restrict__ rp, const int32_t* _
             }
             float x[kU][E];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) Chunk<DT>::load(X, j[u], K, q, x[u]);
+            for (int u = 0; u < kU; ++u) Chunk<DT>::load(at(j[u]), j[u], K, q, x[u]);
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
 #pragma unroll
@@ -1329,6 +1335,9 @@ __device__ inline void gs_block(const int32_t* __restrict__ rp, const int32_t* _
 #pragma unroll
                 for (int i = 0; i < E; ++i) y[i] = y[i] / dd;
                 Chunk<DT>::store(X, r, K, l, y);
+            } else if (FROM) {
+                Chunk<DT>::load(X0, r, K, l, y);
+                Chunk<DT>::store(X, r, K, l, y);
             }
         }
         if (split && tid < kWave) {
@@ -1368,6 +1377,9 @@ __device__ inline void gs_block(const int32_t* __restrict__ rp, const int32_t* _
 #pragma unroll
                     for (int i = 0; i < E; ++i) y[i] = y[i] / dd;
                     Chunk<DT>::store(X, r, K, qq, y);
+                } else if (FROM && f0 == 0) {
+                    Chunk<DT>::load(X0, r, K, qq, y);
+                    Chunk<DT>::store(X, r, K, qq, y);
                 }
                 if (tid == 0) splitcnt[row] = 0;
             }
@@ -1378,14 +1390,19 @@ __device__ inline void gs_block(const int32_t* __restrict__ rp, const int32_t* _
 #pragma unroll
         for (int i = 0; i < E; ++i) y[i] = acc[i] / d;
         Chunk<DT>::store(X, r, K, q, y);
+    } else if (FROM && p == 0 && valid) {
+        float y[E];
+        Chunk<DT>::load(X0, r, K, q, y);
+        Chunk<DT>::store(X, r, K, q, y);
     }
 }
 
-template <int Q, int DT>
+template <int Q, int DT, bool FROM>
 __global__ void __launch_bounds__(kBig) k_gs_step(const int32_t* __restrict__ rp,
                                                   const int32_t* __restrict__ col,
                                                   const float* __restrict__ w,
-                                                  void* __restrict__ X, int32_t K, GsTiers tt,
+                                                  void* __restrict__ X,
+                                                  const void* __restrict__ X0, int32_t K, GsTiers tt,
                                                   float* __restrict__ part,
                                                   int32_t* __restrict__ splitcnt) {
     __shared__ float sacc[kBig / kWave][Q][Chunk<DT>::E];
@@ -1393,7 +1410,7 @@ __global__ void __launch_bounds__(kBig) k_gs_step(const int32_t* __restrict__ rp
     int64_t b = blockIdx.x;
     const int64_t b0 = tt.blk0[tt.split], nb = tt.blk0[tt.nt];
     if (tt.reverse && b >= b0) b = b0 + (nb - 1 - b);
-    gs_block<Q, DT>(rp, col, w, X, K, tt, b, part, splitcnt, sacc, sd);
+    gs_block<Q, DT, FROM>(rp, col, w, X, X0, K, tt, b, part, splitcnt, sacc, sd);
 }
 
 // ------------------------------------------- GS sweeps in one launch
@@ -1780,7 +1797,7 @@ static GsTiers plan_gs_step(const OrderedGraph* og, int Q, int c) {
 }
 
 template <int Q, int DT>
-static int smooth_q(const OrderedGraph* og, int K, int sweeps, void* X, Arena& ws,
+static int smooth_q(const OrderedGraph* og, int K, int sweeps, void* X, const void* X0, Arena& ws,
                     hipStream_t st) {
     const bool pr = prof::on();
     const int xs = DT == GR_BF16 ? 2 : 4;
@@ -1849,7 +1866,7 @@ static int smooth_q(const OrderedGraph* og, int K, int sweeps, void* X, Arena& w
             GR_HIP(hipMemcpyAsync(table, host.data(), host.size(), hipMemcpyHostToDevice, st));
             const int64_t chunks = (int64_t)(vector / 16);
             hipLaunchKernelGGL(k_gs_flow_start, dim3(std::min(2048u, blocks_for(chunks * (sweeps + 1), 256))),
-                               dim3(256), 0, st, (const gs_v4*)X, (gs_v4*)B, chunks,
+                               dim3(256), 0, st, (const gs_v4*)(X0 ? X0 : X), (gs_v4*)B, chunks,
                                chunks * (sweeps + 1), part, words, status);
             GR_LAUNCHED("gs flow start");
             const int32_t *rp = og->g.row_ptr, *col = og->g.col;
@@ -1901,8 +1918,9 @@ static int smooth_q(const OrderedGraph* og, int K, int sweeps, void* X, Arena& w
             if (tt.nt == 0) continue;
             tt.reverse = alternate ? (int32_t)(launched & 1) : 0;
             ++launched;
-            hipLaunchKernelGGL((k_gs_step<Q, DT>), dim3((unsigned)tt.blk0[tt.nt]), dim3(kBig), 0, st,
-                               og->g.row_ptr, og->g.col, og->g.w, X, K, tt, part, splitcnt);
+            hipLaunchKernelGGL((X0 && s == 0 ? k_gs_step<Q, DT, true> : k_gs_step<Q, DT, false>),
+                               dim3((unsigned)tt.blk0[tt.nt]), dim3(kBig), 0, st, og->g.row_ptr,
+                               og->g.col, og->g.w, X, X0, K, tt, part, splitcnt);
             GR_LAUNCHED("gs step");
         }
     if (pr) prof::end(st, prof::SMOOTH, sweep_bytes * sweeps, (int64_t)steps * sweeps);
@@ -1911,24 +1929,24 @@ static int smooth_q(const OrderedGraph* og, int K, int sweeps, void* X, Arena& w
 }
 
 int smooth_ordered(const OrderedGraph* og, int32_t K, int32_t sweeps, int32_t dtype, void* X,
-                   Arena& ws, hipStream_t st) {
+                   Arena& ws, hipStream_t st, const void* X0) {
     if (og->g.n == 0 || sweeps == 0) return GR_OK;
     int bytes = K * (dtype == GR_BF16 ? 2 : 4);
     int Q = bytes / 16;
     if (dtype == GR_BF16) {
         switch (Q) {
-            case 1: return smooth_q<1, GR_BF16>(og, K, sweeps, X, ws, st);
-            case 2: return smooth_q<2, GR_BF16>(og, K, sweeps, X, ws, st);
-            case 4: return smooth_q<4, GR_BF16>(og, K, sweeps, X, ws, st);
-            case 8: return smooth_q<8, GR_BF16>(og, K, sweeps, X, ws, st);
+            case 1: return smooth_q<1, GR_BF16>(og, K, sweeps, X, X0, ws, st);
+            case 2: return smooth_q<2, GR_BF16>(og, K, sweeps, X, X0, ws, st);
+            case 4: return smooth_q<4, GR_BF16>(og, K, sweeps, X, X0, ws, st);
+            case 8: return smooth_q<8, GR_BF16>(og, K, sweeps, X, X0, ws, st);
         }
     } else {
         switch (Q) {
-            case 1: return smooth_q<1, GR_F32>(og, K, sweeps, X, ws, st);
-            case 2: return smooth_q<2, GR_F32>(og, K, sweeps, X, ws, st);
-            case 4: return smooth_q<4, GR_F32>(og, K, sweeps, X, ws, st);
-            case 8: return smooth_q<8, GR_F32>(og, K, sweeps, X, ws, st);
-            case 16: return smooth_q<16, GR_F32>(og, K, sweeps, X, ws, st);
+            case 1: return smooth_q<1, GR_F32>(og, K, sweeps, X, X0, ws, st);
+            case 2: return smooth_q<2, GR_F32>(og, K, sweeps, X, X0, ws, st);
+            case 4: return smooth_q<4, GR_F32>(og, K, sweeps, X, X0, ws, st);
+            case 8: return smooth_q<8, GR_F32>(og, K, sweeps, X, X0, ws, st);
+            case 16: return smooth_q<16, GR_F32>(og, K, sweeps, X, X0, ws, st);
         }
     }
     return set_error(GR_EUNSUP, "unsupported K=%d for this dtype", K);
