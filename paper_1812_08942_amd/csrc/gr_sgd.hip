@@ -231,11 +231,16 @@ __global__ void k_copy_scalar(double* __restrict__ sc, int from, int to) {
 //    have) means not there yet.  Waiting for z to be stored before the sums
 //    are published cost 2 us of each iteration.
 //  * Emptying.  Slots go round in four epochs: a workgroup empties its slot
-//    of epoch e + 2 once epoch e is complete (all have then passed e - 1 and
-//    with it e - 2).  z has two buffers: once the product's meeting of
-//    iteration i + 1 is complete everyone has read z of iteration i, and it
-//    is emptied.  Every publication of a product's sum first waits for the
-//    thread's stores, and comes between an emptying and the next use.
+//    of epoch e + 3 once epoch e is complete.  That is the slot of e - 1,
+//    which everyone has read before publishing e.  The slot's next reader has
+//    seen the publications of e + 1 and e + 2, one of which is a product's
+//    sum, and every publication of a product's sum first waits for the
+//    thread's stores: the emptying has arrived before it.  (The slot of e + 2
+//    is too late: after a product's meeting e only the publication of e + 1,
+//    which does not wait, would lie between.)  z has two buffers: once the
+//    product's meeting of iteration i + 1 is complete everyone has read z of
+//    iteration i, and it is emptied; the next reader of that buffer has seen
+//    the product's meeting of iteration i + 2, whose publication waits.
 //  * Every wait is bounded; past it the call fails.
 // A meeting of 64 workgroups takes 1.5 us when each has a line of its own for
 // its slots, 2.1 us when the slots share lines; counting arrivals and reading
@@ -251,6 +256,7 @@ constexpr int kResRows = kResN / kResBlocks;  // rows of a workgroup at most
 constexpr int kResPieces = 2048;              // pieces of a workgroup at most
 constexpr unsigned kResSpin = 1u << 21;
 constexpr int kResEpochs = 4;
+constexpr int kResAhead = 3;  // epochs from a meeting to the slot it empties
 constexpr int kResLine = 8;  // words from one workgroup's slots to the next's: a line each
 constexpr size_t kResSlotWords = (size_t)kResEpochs * kResBlocks * kResLine;
 constexpr unsigned long long kResEmpty = ~0ull;
@@ -349,7 +355,7 @@ struct ResMeet {
             sh.sum[1] = y;
             if (!ok) abandon(sh);
         }
-        if (lane < 2) st_agent(at(epoch + 2, blockIdx.x) + lane, kResEmpty);
+        if (lane < 2) st_agent(at(epoch + kResAhead, blockIdx.x) + lane, kResEmpty);
     }
     // all threads: waits for the sums; false when a wait ran out, here or
     // elsewhere
