@@ -13,6 +13,7 @@
 #include "gr_internal.hpp"
 
 #include <math.h>
+#include <stdlib.h>
 #include <string.h>
 
 #include <vector>
@@ -749,7 +750,7 @@ struct Sgd {
     unsigned long long* words;  // slots and z of the resident solve
     int32_t* status;
     double* b0;  // L_G h_0
-    bool resident;
+    bool resident, demanded;
     hipStream_t st;
     int cg_max;
     double cg_tol;
@@ -762,9 +763,13 @@ struct Sgd {
         t2 = ws.take<double>(n + 1);
         resident = false;
     }
-    // whether the solves on the current P run in one launch each
+    // whether the solves on the current P run in one launch each.
+    // GR_CG_RESIDENT=0 turns that off; with 1 a call whose solves cannot
+    // fails (tests of which way was taken).
     int plan_resident() {
-        resident = n > 0 && n <= kResN && nnzP <= kResNnz;
+        const char* env = getenv("GR_CG_RESIDENT");
+        demanded = env && env[0] == '1';
+        resident = n > 0 && n <= kResN && nnzP <= kResNnz && !(env && env[0] == '0');
         if (resident) {
             int dev = 0, cus = 0, per_cu = 0;
             GR_HIP(hipGetDevice(&dev));
@@ -773,8 +778,9 @@ struct Sgd {
                 &per_cu, (const void*)k_cg_resident, kResThreads, 0));
             resident = (int64_t)cus * per_cu >= kResBlocks;
         }
-        return GR_OK;
+        return resident || !demanded ? GR_OK : unfit();
     }
+    static int unfit() { return set_error(GR_EUNSUP, "the solve does not fit one launch"); }
     int solve_resident(const double* b, double* out) {
         GR_HIP(hipMemsetAsync(words, 0xff, sizeof(unsigned long long) * res_words(n), st));
         const int32_t *rpv = rpP, *cv = colP;
@@ -901,6 +907,7 @@ struct Sgd {
             int32_t state[RES_WORDS];
             memcpy(state, hs + SC_STATUS, sizeof(state));
             if (state[RES_FLAGS] & RES_UNFIT) {  // some workgroup's rows do not fit: by launches
+                if (demanded) return unfit();
                 resident = false;
                 return power_vector(seed, t_iters, lam, lam1);
             }
