@@ -242,7 +242,8 @@ __global__ void k_copy_scalar(double* __restrict__ sc, int from, int to) {
 //    product's meeting of iteration i + 1 is complete everyone has read z of
 //    iteration i, and it is emptied; the next reader of that buffer has seen
 //    the product's meeting of iteration i + 2, whose publication waits.
-//  * Every wait is bounded; past it the call fails.
+//  * Every wait is bounded (about 2 s); where one runs out, as on a card that
+//    other work keeps busy, the call goes on by launches.
 // A meeting of 64 workgroups takes 1.5 us when each has a line of its own for
 // its slots, 2.1 us when the slots share lines; counting arrivals and reading
 // the sums afterwards takes 2.2 us.
@@ -319,6 +320,7 @@ struct ResShared {
 struct ResMeet {
     unsigned long long* slots;
     int32_t* status;
+    unsigned spin_limit;
     unsigned epoch;
 
     // publishes the workgroup's sums of a and b (one pair per thread)
@@ -344,7 +346,7 @@ struct ResMeet {
         const unsigned long long* mine = at(epoch, lane);
         unsigned long long u = kResEmpty, v = kResEmpty;
         bool ok = false;
-        for (unsigned it = 0; it < kResSpin; ++it) {
+        for (unsigned it = 0; it < spin_limit; ++it) {
             if (u == kResEmpty) u = ld_agent(mine);
             if (v == kResEmpty) v = ld_agent(mine + 1);
             ok = __ballot(u == kResEmpty || v == kResEmpty) == 0;
@@ -430,7 +432,7 @@ __device__ inline unsigned long long res_wait(ResShared& sh, ResMeet& meet,
                                               unsigned hi) {
     unsigned long long v = ((unsigned long long)hi << 32) | lo;
     for (unsigned it = 0; v == kResEmpty; ++it) {
-        if (it >= kResSpin || ((it & 1023u) == 1023u && meet.aborted())) {
+        if (it >= meet.spin_limit || ((it & 1023u) == 1023u && meet.aborted())) {
             meet.abandon(sh);
             break;
         }
@@ -473,9 +475,9 @@ __device__ inline void res_take(ResShared& sh, ResMeet& meet, const unsigned lon
 __global__ void __launch_bounds__(kResThreads) k_cg_resident(
     const int32_t* __restrict__ rp, const int32_t* __restrict__ col, const double* __restrict__ w,
     const double* __restrict__ diag, int32_t n, const double* __restrict__ b, double* __restrict__ out,
-    unsigned long long* words, int32_t* status, int32_t cg_max, double tol2) {
+    unsigned long long* words, int32_t* status, int32_t cg_max, double tol2, unsigned spin_limit) {
     __shared__ ResShared sh;
-    ResMeet meet{words, status, 0u};
+    ResMeet meet{words, status, spin_limit, 0u};
     unsigned long long* const zbuf = words + kResSlotWords;
     const int tid = threadIdx.x, blk = blockIdx.x;
     const int R = (n + kResBlocks - 1) / kResBlocks;  // at most kResRows
@@ -750,7 +752,8 @@ struct Sgd {
     unsigned long long* words;  // slots and z of the resident solve
     int32_t* status;
     double* b0;  // L_G h_0
-    bool resident, demanded;
+    bool resident, demanded, timed_out;
+    unsigned spin_limit;
     hipStream_t st;
     int cg_max;
     double cg_tol;
@@ -761,14 +764,23 @@ struct Sgd {
         status = reinterpret_cast<int32_t*>(sc + SC_STATUS);
         b0 = ws.take<double>(n + 1);
         t2 = ws.take<double>(n + 1);
-        resident = false;
+        resident = timed_out = false;
     }
     // whether the solves on the current P run in one launch each.
     // GR_CG_RESIDENT=0 turns that off; with 1 a call whose solves cannot
-    // fails (tests of which way was taken).
+    // fails (tests of which way was taken).  GR_CG_SPIN_LIMIT=k ends a wait
+    // after k polls (tests of the way out by launches, which a call that has
+    // taken it does not leave again).
     int plan_resident() {
+        resident = false;
+        if (timed_out) return GR_OK;
         const char* env = getenv("GR_CG_RESIDENT");
         demanded = env && env[0] == '1';
+        spin_limit = kResSpin;
+        if (const char* sl = getenv("GR_CG_SPIN_LIMIT")) {
+            const long v = atol(sl);
+            if (v > 0 && v < (long)kResSpin) spin_limit = (unsigned)v;
+        }
         resident = n > 0 && n <= kResN && nnzP <= kResNnz && !(env && env[0] == '0');
         if (resident) {
             int dev = 0, cus = 0, per_cu = 0;
@@ -789,7 +801,7 @@ struct Sgd {
         double tol2 = cg_tol * cg_tol;
         void* args[] = {(void*)&rpv, (void*)&cv, (void*)&wv, (void*)&dv, (void*)&nn, (void*)&b,
                         (void*)&out, (void*)&words, (void*)&status, (void*)&cm,
-                        (void*)&tol2};
+                        (void*)&tol2, (void*)&spin_limit};
         GR_HIP(hipLaunchCooperativeKernel((const void*)k_cg_resident, dim3(kResBlocks),
                                           dim3(kResThreads), args, 0, st));
         return GR_OK;
@@ -906,13 +918,15 @@ struct Sgd {
         if (resident) {
             int32_t state[RES_WORDS];
             memcpy(state, hs + SC_STATUS, sizeof(state));
-            if (state[RES_FLAGS] & RES_UNFIT) {  // some workgroup's rows do not fit: by launches
-                if (demanded) return unfit();
+            // a wait ran out (what the solves after it say is then void), or
+            // some workgroup's rows do not fit: again by launches
+            if (state[RES_FLAGS] & (RES_TIMEOUT | RES_UNFIT)) {
+                if (state[RES_FLAGS] & RES_TIMEOUT) timed_out = true;
+                else if (demanded) return unfit();
                 resident = false;
                 return power_vector(seed, t_iters, lam, lam1);
             }
             if (state[RES_FLAGS] & RES_DIVERGED) return set_error(GR_EHIP, "CG diverged");
-            if (state[RES_FLAGS] & RES_TIMEOUT) return set_error(GR_EHIP, "CG wait timed out");
             cg_iters_max = std::max<int64_t>(cg_iters_max, state[RES_ITERS]);
         }
         if (!(*lam == *lam)) return set_error(GR_EHIP, "lambda_n is not finite");

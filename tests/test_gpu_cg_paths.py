@@ -72,3 +72,25 @@ def test_by_launches_where_they_do_not_fit(name, monkeypatch):
     with pytest.raises(G.GraphReduceError) as e:
         run()
     assert e.value.code == -6
+
+
+def test_a_wait_that_runs_out_goes_on_by_launches(monkeypatch):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1812_08942_amd import graphreduce as G
+
+    g, wP = _graph("4097")
+    dg = G.DeviceGraph.from_numpy(g.row_ptr, g.col, g.w, "cuda:0")
+    edges = G.gr_edge_list(dg)
+    out = {}
+    for name, value in (("GR_CG_RESIDENT", "0"), ("GR_CG_SPIN_LIMIT", "1")):
+        print(f"[gpu-case] CG wait {name}={value}", flush=True)
+        with monkeypatch.context() as m:
+            m.setenv(name, value)
+            w = torch.from_numpy(wP.copy()).to("cuda:0")
+            rep = G.gr_sgd_scale(dg, dg, edges, w, k_max=3, seed=9)
+            keep, _, spars = G.gr_sparsify(dg, rounds=2, add_frac=0.05, seed=7)
+            out[name] = rep, w.cpu().numpy(), keep.cpu().numpy(), spars
+    a, b = out["GR_CG_RESIDENT"], out["GR_CG_SPIN_LIMIT"]
+    assert a[0] == b[0] and a[3] == b[3]
+    assert np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
