@@ -210,6 +210,9 @@ int gr_init_vectors(int64_t n, int32_t K, uint64_t seed, int32_t dtype, void* X,
  * sum_j w_vj x_j / d_v.  `colours` is a valid colouring (device int32[n]);
  * GR_ECOLOUR if a colour is out of range.  X: device [n][K] of `dtype`.
  * Internally relabels the graph colour-major once per call.
+ * Inf and NaN: on rows of up to 32 entries x_v itself does not enter, as in the
+ * formula; on wider rows it may, with weight 0, so that an x_v which is not
+ * finite can make the row NaN although its neighbours are finite.
  */
 int gr_smooth(const gr_graph* g, const int32_t* colours, int32_t n_colours, int32_t K,
               int32_t sweeps, int32_t dtype, void* X, void* ws, size_t ws_bytes,
