@@ -716,14 +716,20 @@ static int cheb_block(int n_eig) {
     return m > kMaxP ? kMaxP : m;
 }
 
+// degrees and inverses, the long rows with their flags and places, the scan's
+// tiles: what setup_operator takes
+static size_t operator_bytes(int64_t n) {
+    const size_t N = (size_t)n + 1;
+    return 16 * N + 12 * N + N / 64;
+}
+
 size_t eig_workspace(int64_t n, int32_t n_eig) {
     (void)n_eig;
-    size_t blk = (size_t)(n + 1) * kMaxP * 8;
-    // blocks, degrees, small matrices; row pieces (at most 2n: offsets, rows,
-    // and partial sums of up to kMaxP columns each)
-    size_t b = 4 * blk + 16 * (size_t)(n + 1) + 8 * (size_t)kRowBlocks * kMaxP * kMaxP +
-               8 * 4 * kMaxP * kMaxP + 16 * (size_t)(n + 1) + 2 * blk +
-               16 * (size_t)(n + 1);  // b^-1/2 and b^1/2 of a generalised problem
+    const size_t blk = (size_t)(n + 1) * kMaxP * 8;
+    // blocks, small matrices, the operator, b^-1/2 and b^1/2 of a generalised
+    // problem
+    size_t b = 4 * blk + 8 * (size_t)kRowBlocks * kMaxP * kMaxP + 8 * 4 * kMaxP * kMaxP +
+               operator_bytes(n) + 16 * (size_t)(n + 1);
     return b + b / 16 + (1u << 20);
 }
 
@@ -1114,8 +1120,7 @@ __global__ void k_sqrt_vec(const double* __restrict__ b, int64_t n, double* __re
 
 size_t jacobi_workspace(int64_t n, int32_t k) {
     const size_t N = (size_t)n + 1;
-    size_t b = 16 * N + 4 * N + 4 * (2 * N) + 8 * (2 * N) * (size_t)k   // operator
-               + 8 * N * (size_t)k + 8 * 64 + 4 * N + (64u << 10);      // L Y, lambda, scan
+    const size_t b = operator_bytes(n) + 8 * N * (size_t)k + 8 * 64;  // and L Y, lambda
     return b + b / 16 + (1u << 20);
 }
 
@@ -1216,9 +1221,12 @@ __global__ void k_fill_f64(double* __restrict__ x, int64_t n, double v) {
 size_t multilevel_workspace(int64_t n, int64_t nnz, int32_t k) {
     (void)nnz;
     const size_t N = (size_t)n + 1;
-    size_t b = eig_workspace(n, k) + 2 * 8 * N * (size_t)k + 2 * 8 * N + jacobi_workspace(n, k) +
-               orthonormalize_workspace(n, k) + restrict_workspace(n, n, 1);
-    return b + b / 16 + (1u << 20);
+    // B of every level (they may shrink slowly) and the degrees, two blocks of
+    // vectors; the phases run one after another in what is left
+    const size_t phase = std::max(std::max(eig_workspace(n, k), jacobi_workspace(n, k)),
+                                  std::max(orthonormalize_workspace(n, k), restrict_workspace(n, n, 1)));
+    const size_t b = 8 * N * (GR_MAX_LEVELS + 2) + 2 * 8 * N * (size_t)k;
+    return b + b / 16 + (1u << 20) + phase;
 }
 
 int multilevel_eigs(const gr_graph* g, const gr_hierarchy* h, int32_t k, int32_t cut, double theta,
