@@ -882,8 +882,7 @@ size_t vjp_workspace(int64_t n, int64_t nnz, int32_t K, int32_t dtype, int32_t S
 template <int DT>
 struct VjpStates {
     const OrderedGraph* og;
-    int K, store;
-    size_t xbytes;
+    int K;
     std::vector<char*> slot;  // store: S + 1 of them; else X_0, two, spares
     std::vector<int> holds;   // the state in each slot, -1 for none
     Arena& ws;
@@ -924,7 +923,6 @@ struct VjpStates {
         if (q < 0) {  // the first pair: X_s is one sweep from X_{s-1}
             GR_TRY(build(s - 1, -1, &p));
             q = p == 1 ? 2 : 1;
-            if (store) q = s;
             GR_TRY(sweep(p, q, 1));
         } else {
             GR_TRY(build(s - 1, q, &p));
@@ -941,7 +939,7 @@ static int vjp_impl(const VjpPlan& pl, int K, int S, int store, void* states, si
     const OrderedGraph* og = pl.og;
     const int C = og->n_colours;
     const size_t xbytes = (size_t)og->g.n * K * (DT == GR_BF16 ? 2 : 4);
-    VjpStates<DT> X{og, K, store, xbytes, {}, {}, ws, st};
+    VjpStates<DT> X{og, K, {}, {}, ws, st};
     for (int s = 0; s < (store ? S + 1 : 3); ++s) X.slot.push_back((char*)states + (size_t)s * xstride);
     if (!store)  // gx, float32, is written after the last reverse step
         for (int s = 0; s < (DT == GR_BF16 ? 2 : 1); ++s) X.slot.push_back((char*)gx + s * xbytes);
