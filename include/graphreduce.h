@@ -24,12 +24,16 @@
  *   all threads, freed at exit).
  * Streams.  `stream` is a hipStream_t (NULL = the null stream).  Work is
  *   enqueued on it; an entry point returns only after the device-to-host
- *   size reads it documents, otherwise asynchronously.
+ *   size reads it documents, otherwise asynchronously.  Such a read polls its
+ *   page: the calling thread keeps a core for as long as the call waits.
  * Errors.  Every entry point returns GR_OK (0) or a negative GR_E* code and
  *   sets a thread-local message readable with gr_last_error().  On error,
  *   outputs are unspecified.  No C++ exception crosses the ABI.
  * Determinism.  Identical inputs, parameters and seeds give bit-identical
- *   outputs: no floating-point atomics are used anywhere.
+ *   outputs: no floating-point atomics are used anywhere.  One exception: a
+ *   solve of gr_sgd_scale, gr_sparsify or gr_spectral_reduce that other work
+ *   on the card holds up for about 2 s goes on launch by launch, whose sums
+ *   have another order (last bits).
  * Vector storage.  Test-vector matrices X are node-major [n][K]: float32
  *   (GR_F32, K a multiple of 4) or bfloat16 (GR_BF16, K a multiple of 8,
  *   round-to-nearest-even on store); arithmetic is float32 in both cases.
