@@ -238,9 +238,9 @@ def run_workload(G, key, dtype, steps, warmup, g=None):
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": measured_traffic(key, dtype),
-            "avg_launch_us": avg_us,
-            "bytes_per_launch": sm["bytes"] / max(1, sm["launches"]),
-            "launches_per_step": sm["launches"] / steps,
+            "avg_colour_step_us": avg_us,
+            "bytes_per_colour_step": sm["bytes"] / max(1, sm["launches"]),
+            "colour_steps_per_step": sm["launches"] / steps,
         },
     }
     return res, (g, wl, r, dg)
