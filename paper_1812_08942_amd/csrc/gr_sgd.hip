@@ -206,7 +206,7 @@ __global__ void k_copy_scalar(double* __restrict__ sc, int from, int to) {
 
 // ------------------------------------------------- CG in one launch
 // The whole solve on graphs of up to kResN nodes.  Launch by launch, an
-// iteration is eight dependent launches and its time is theirs (31 us at
+// iteration is eight dependent launches and its time is theirs (35 us at
 // 13,000 nodes and 280,000 entries, whatever the kernels do); here
 // kResBlocks workgroups stay resident (cooperative launch) and meet twice
 // per iteration, which then takes 8 us (product 1.3, meetings 1.9 and 2.9,
